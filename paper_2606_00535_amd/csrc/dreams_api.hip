@@ -484,54 +484,76 @@ dreams_status_t dreams_tree_accept(int32_t batch, int32_t num_nodes, int32_t voc
 }
 
 // ------------------------------------------------------------------------------------- sampled acceptance
-constexpr long long kSampledLargeFrom = 4096;   // stats workgroups beyond which pieces are large
+// Row-form workgroups (pieces of 4096 entries of every row) beyond which the walk form is taken.  The row form's time
+// grows with its workgroups, the walk form's with the rows visited (about 6 us each; trees 4 to 8 deep, drafts
+// that follow the target): 576 workgroups (8 x 9 rows of 32000) 23.6 against 44 us, 960 (2 x 60 of 32000) 35.6
+// against 30.5, 1440 44.5 against 32.7, 2048 (16 x 128 of 1000) 46.5 against 31, 2280 (60 of 152064) 82 against 42.
+// (A chain of dozens of drafts that are all kept is the walk form's worst case.)
+constexpr long long kSampledWalkFrom = 1024;
+// Vocabularies that one workgroup walks alone: no exchange at all (128 nodes x 1000 entries: 2 us a row).
+constexpr int kSampledWalkAlone = 8192;
+constexpr long long kSampledMaxVocab = 1ll << 23;
 
 struct SampledPlan {
-  int sub_pieces, chunks, row_stride;
-  size_t row_base, piece_off, mass_off, flag_off, bytes;
+  int walk, part, sub_pieces, chunks, row_stride;
+  size_t row_base, slot_off, mass_off, flag_off, bytes;
 };
 
-dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, SampledPlan* p) {
+// cus: compute units of the device (the workspace's size does not depend on it)
+dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPlan* p) {
   if (B < 0) return fail(DREAMS_ERR_INVALID_ARG, "batch = %d < 0", B);
   if (T < 1 || T > kMaxNodes) return fail(DREAMS_ERR_INVALID_ARG, "num_nodes = %d outside [1, %d]", T, kMaxNodes);
   if (V < 1) return fail(DREAMS_ERR_INVALID_ARG, "vocab = %d < 1", V);
   *p = SampledPlan{};
   if (B == 0) return DREAMS_OK;
-  // pieces of 4096 entries while there are at most 16 statistics workgroups per compute unit (the wait chain
-  // dominates: each piece computes p and q before it waits, and fewer pieces a row wait for fewer arrivals:
-  // llava7b_layer 29.5 -> 28.6 us, llava13b_layer 140 (split form) -> 114 us, against 2048-entry pieces);
-  // beyond that, pieces of 8192 entries in four parts (the split form, each part streamed after the waits)
-  const long long small = (long long)kSampledThreads * kSampledPerThreadRow;
-  const long long large = (long long)kSampledThreads * kSampledPerThread * kSampledSubLarge;
-  long long sub = 1, chunks = ((long long)V + small - 1) / small;
-  if ((long long)B * T * chunks > kSampledLargeFrom || chunks > kSampledMaxChunks) {
-    sub = kSampledSubLarge;
-    chunks = ((long long)V + large - 1) / large;
-  }
-  if (chunks > kSampledMaxChunks)
-    return fail(DREAMS_ERR_UNSUPPORTED, "vocab = %d exceeds %lld", V, (long long)kSampledMaxChunks * large);
-  if ((long long)B * (2 * T - 1) * chunks > 0x7fffffffLL) return fail(DREAMS_ERR_UNSUPPORTED, "problem too large");
-  // counter region: one word per sequence, then a block of 4, 8 or 16 words per row (as many as fit)
+  if (V > kSampledMaxVocab) return fail(DREAMS_ERR_UNSUPPORTED, "vocab = %d exceeds %lld", V, kSampledMaxVocab);
   const size_t rows = (size_t)B * T, base = ((size_t)B + 63) / 64 * 64;
   if (base + rows * 4 > kMaxCounters)
     return fail(DREAMS_ERR_UNSUPPORTED, "batch * num_nodes = %zu rows exceed the arrival counters (%zu)", rows,
                 (kMaxCounters - base) / 4);
-  size_t stride = 16;
-  while (stride > 4 && base + rows * stride > kMaxCounters) stride >>= 1;
-  p->sub_pieces = (int)sub;
-  p->chunks = (int)chunks;
-  p->row_stride = (int)stride;
-  p->row_base = base;
+  auto pieces = [&](long long part) { return ((long long)V + part - 1) / part; };
+  // the pieces' slots get 32 bytes per row and 4096 vocabulary entries (8192 where those are many), their masses
+  // eight (the walk form's slots take both), then every row's decision and token
+  long long units = pieces(4096);
+  if ((long long)rows * units > 4096 || units > 1024) units = pieces(8192);
   size_t off = kCounterBytes;
   auto take = [&](size_t bytes) {
     const size_t at = off;
     off += (bytes + 255) / 256 * 256;
     return at;
   };
-  p->piece_off = take(rows * chunks * 4 * sizeof(double));
-  p->mass_off = take(rows * chunks * sizeof(double));
+  p->slot_off = take(rows * units * 32);
+  p->mass_off = take(rows * units * 8);
   p->flag_off = take(rows * 2 * sizeof(int32_t));
   p->bytes = off;
+
+  long long part = kSampledRowPart, sub = 1;
+  const bool walk = (long long)rows * pieces(part) > kSampledWalkFrom || pieces(part) > kSampledMaxPieces;
+  auto fits = [&] {
+    const long long n = pieces(part * sub);
+    return n <= kSampledMaxPieces && (n == 1 || B * n * kSampledWalkSlotBytes <= (long long)(p->flag_off - p->slot_off));
+  };
+  if (walk) {
+    // the smallest part of which the batch's pieces take a compute unit each, so that all of them run at once on
+    // as many units as there are; the largest, in rounds of sequences, for larger batches
+    for (long long size : kSampledParts) {
+      part = size;
+      if (V <= kSampledWalkAlone ? pieces(part) == 1 : fits() && B * pieces(part) <= cus) break;
+    }
+    if (!fits()) {
+      part = kSampledStreamPart;
+      for (sub = 2; !fits();) ++sub;
+    }
+  }
+  const long long chunks = pieces(part * sub);
+  size_t stride = 16;
+  while (stride > 4 && base + rows * stride > kMaxCounters) stride >>= 1;
+  p->walk = walk ? 1 : 0;
+  p->part = (int)part;
+  p->sub_pieces = (int)sub;
+  p->chunks = (int)chunks;
+  p->row_stride = (int)stride;
+  p->row_base = base;
   return DREAMS_OK;
 }
 
@@ -539,7 +561,7 @@ dreams_status_t dreams_tree_accept_sampled_workspace_size(int32_t batch, int32_t
                                                           size_t* bytes) {
   if (!bytes) return fail(DREAMS_ERR_INVALID_ARG, "bytes is NULL");
   SampledPlan p;
-  dreams_status_t st = plan_sampled(batch, num_nodes, vocab, &p);
+  dreams_status_t st = plan_sampled(batch, num_nodes, vocab, 256, &p);
   if (st != DREAMS_OK) return st;
   *bytes = p.bytes;
   return ok();
@@ -552,7 +574,7 @@ dreams_status_t dreams_tree_accept_sampled(int32_t batch, int32_t num_nodes, int
                                            int32_t* next_token, void* workspace, size_t workspace_bytes,
                                            hipStream_t stream) {
   SampledPlan p;
-  dreams_status_t st = plan_sampled(batch, num_nodes, vocab, &p);
+  dreams_status_t st = plan_sampled(batch, num_nodes, vocab, 256, &p);
   if (st != DREAMS_OK) return st;
   if (!(temperature > 0.0) || !isfinite(temperature))
     return fail(DREAMS_ERR_INVALID_ARG, "temperature = %g is not a positive finite number", temperature);
@@ -570,6 +592,10 @@ dreams_status_t dreams_tree_accept_sampled(int32_t batch, int32_t num_nodes, int
     return fail(DREAMS_ERR_WORKSPACE, "workspace has %zu bytes, %zu are needed", workspace_bytes, p.bytes);
   if (!aligned(workspace, 256)) return fail(DREAMS_ERR_WORKSPACE, "workspace must be 256-byte aligned");
 
+  int cus = 0;
+  st = device_cus(&cus);
+  if (st == DREAMS_OK) st = plan_sampled(batch, num_nodes, vocab, cus, &p);
+  if (st != DREAMS_OK) return st;
   SampledArgs a{};
   a.target_logits = target_logits;
   a.draft_logits = draft_logits;
@@ -582,9 +608,9 @@ dreams_status_t dreams_tree_accept_sampled(int32_t batch, int32_t num_nodes, int
   char* ws = (char*)workspace;
   uint32_t* ctr = (uint32_t*)ws;
   a.seq_ctr = ctr;
-  a.row_words = ctr + p.row_base;
+  a.row_ctr = ctr + p.row_base;
   a.row_stride = p.row_stride;
-  a.piece_stat = (double*)(ws + p.piece_off);
+  a.slots = (uint64_t*)(ws + p.slot_off);
   a.mass = (double*)(ws + p.mass_off);
   a.kept = (int32_t*)(ws + p.flag_off);
   a.final_token = a.kept + (size_t)batch * num_nodes;
@@ -593,6 +619,8 @@ dreams_status_t dreams_tree_accept_sampled(int32_t batch, int32_t num_nodes, int
   a.T = num_nodes;
   a.V = vocab;
   a.chunks = p.chunks;
+  a.walk = p.walk;
+  a.part = p.part;
   a.sub_pieces = p.sub_pieces;
   a.vec4 = (vocab % 4 == 0) && aligned(target_logits, 16) && aligned(draft_logits, 16);
   a.err = ctr + kErrorWord;

@@ -193,18 +193,17 @@ struct AcceptArgs {
 hipError_t launch_tree_accept(const AcceptArgs& a, hipStream_t stream);
 
 // ------------------------------------------------------------------------------- sampled acceptance
-// Every row of B * T vocabulary rows is cut into pieces.  With one-part pieces (4096 entries, a thread holding
-// kSampledPerThreadRow consecutive entries) the launch has one workgroup per piece of every row, in row order:
-// the piece's statistics, then the residual masses and accept decisions of the row's children, then (one
-// piece per row) the token emitted if the walk ends there.  With four-part pieces (many pieces: 4 sub-pieces
-// of 2048 entries, a thread holding kSampledPerThread consecutive entries of each) it has, in blockIdx order,
-// first one per piece of every row ("stats" pieces: maxima and normalisers), then one per piece of every
-// child node c, by c ("pass" pieces: the residual mass after c's rejection, and c's own accept decision).
-constexpr int kSampledThreads = 256;
-constexpr int kSampledPerThread = 8;
-constexpr int kSampledPerThreadRow = 16;
-constexpr int kSampledSubLarge = 4;         // sub-pieces per piece for problems of many pieces (else 1)
-constexpr int kSampledMaxChunks = 1024;     // pieces per row, at most
+// Every vocabulary row is cut into pieces.  Row form: a workgroup per piece of every row, in row order (pieces of
+// 4096 entries).  Walk form: a workgroup per piece of every sequence, which takes only the rows that the
+// sequence's walk visits, one after the other: pieces of one part (2048 to 10240 entries, whose probabilities
+// stay in registers) or, for vocabularies that this does not hold, of several parts of 8192.
+constexpr int kSampledRowPart = 4096;
+constexpr int kSampledParts[] = {2048, 4096, 8192, 10240};
+constexpr int kSampledStreamPart = 8192;
+constexpr int kSampledMaxPieces = 64;       // pieces per row, at most: one wave reads all of their slots
+constexpr int kSampledRowCounter = 2;       // a row's words: its child word (64 bits), then its counter
+constexpr int kSampledRowSlotBytes = 32;    // a piece's exchange slots
+constexpr int kSampledWalkSlotBytes = 64;
 
 struct SampledArgs {
   const float* target_logits;  // [B, T, V]
@@ -215,18 +214,19 @@ struct SampledArgs {
   int32_t* accept_len;         // [B]
   int32_t* accept_path;        // [B, T]
   int32_t* next_token;         // [B]
-  uint32_t* seq_ctr;           // [B] rows finished per sequence
-  uint32_t* row_words;         // [B * T] blocks of row_stride words: a 64-bit residual accumulator (arrivals in
-                               // the top 11 bits, the fixed-point mass in the low 53), then the stats arrivals
-  int row_stride;              // words per block: 4, 8 or 16
-  double* piece_stat;          // [B, T, chunks, 4] per piece: target maximum and sum of exp((l - max) / tau)
-                               // relative to it, then the same for the draft
-  double* mass;                // [B, T, chunks] residual mass of each piece after rejecting child c
-  int32_t* kept;               // [B, T] child c's decision
-  int32_t* final_token;        // [B, T] the token emitted if the walk ends at node i
+  uint32_t* seq_ctr;           // [B] row form: rows finished; walk form: pieces entered and left
+  uint32_t* row_ctr;           // [B * T] row form: the words of every row, row_stride words apart: as a child, its
+                               // residual mass, decision and arrivals; as a row, pieces entered and left
+  int row_stride;
+  double* mass;                // [B, T, chunks] row form: residual mass of each piece after rejecting child c
+  uint64_t* slots;             // [B (row form: B * T), chunks] the pieces' exchange slots
+  int32_t* kept;               // [B, T] child c's decision (row form)
+  int32_t* final_token;        // [B, T] the token emitted if the walk ends at node i (row form)
   double inv_tau;              // 1 / temperature (may be +inf)
   int B, T, V, chunks;
-  int sub_pieces;              // 1 or kSampledSubLarge
+  int walk;                    // 1: the walk form
+  int part;                    // entries of a part
+  int sub_pieces;              // parts per piece (1: held in registers)
   int vec4;                    // both logits tensors 16-byte aligned and V % 4 == 0
   uint32_t* err;               // the workspace's failure flags
   uint64_t wait_ticks;         // bound on every wait for another workgroup (100 MHz real-time ticks)

@@ -9,43 +9,49 @@
 //
 // The residual after k rejections at a node has the closed form r_k = max(p - C_k q, 0) / D_k, with C_0 = 0,
 // D_0 = 1, and after rejecting one more child C_{k+1} = C_k + D_k, D_{k+1} = sum_x max(p - C_{k+1} q, 0) (both
-// unchanged when that sum is zero).  So the children of a node need only the node's own p and q: one workgroup
-// per piece of each row (2048 entries, each thread holding 8, or 8192 in four parts for problems of many
-// pieces) keeps that piece's logits in registers for the whole call and
-//   (1) computes the piece's maxima and sums of exp((l - max) / tau), target and draft, and waits for the row's
-//       other pieces; every piece then merges the row's statistics itself, in piece order (the same bits
-//       everywhere), and forms p and q of its entries;
-//   (2) takes the node's children in index order: child c, token x, is decided by the piece holding x
-//       (u q(x) D < max(p(x) - C q(x), 0)) against the state its earlier siblings left; each piece adds its part
-//       of c's residual mass sum max(p - (C + D) q, 0) and its arrival to c's 64-bit accumulator in one atomic
-//       (fixed point, units of 2^-51, so the sum does not depend on the order of arrival) and waits for the
-//       whole sum before the next child -- a chain of waits as long as the node's sibling group, among the
-//       row's own pieces;
-//   (3) draws the token emitted if the walk ends at the node: the prefix of the piece masses (of the last
-//       child that moved the state, or of p) finds the piece where the cumulative mass first exceeds
-//       u0 * total, and that piece alone finds the token by a block scan; the row's last piece to finish
-//       counts the row as done;
-//   (4) the sequence's last row to finish walks the tree by ballots (the first kept child of each node) and
-//       emits the token prepared for the node it stops at.
-// Problems of many pieces (pieces of four 2048-entry parts) use a split form instead, with twice the workgroups:
-// first a "stats" workgroup per piece of every row (its last piece draws a leaf's token), then a "pass"
-// workgroup per piece of every child c, by c, which merges the parent's statistics, computes p and q of the
-// parent's piece and adds c's part of the residual mass once the earlier siblings' sums are complete; the last
-// piece of a node's last child draws the node's token.  (At gqa_long's 16 x 128 x 152064 it takes 1.8 ms
-// against 2.7 ms for the row-piece form, whose pieces re-stream their parts for every child.)
+// unchanged when that sum is zero).  So the children of a node need only the node's own p and q.  A vocabulary
+// row is cut into pieces, a workgroup each, which keep their entries in registers and
+//   (1) compute the piece's maxima and sums of exp((l - max) / tau), target and draft, exchange them, and merge
+//       the row's statistics themselves, in the same order (the same bits everywhere): p and q;
+//   (2) take the node's children in index order: child c, token x, is decided by the piece holding x
+//       (u q(x) D < max(p(x) - C q(x), 0)) against the state its earlier siblings left; the pieces exchange that
+//       decision with their parts of c's residual mass sum max(p - (C + D) q, 0), which moves the state;
+//   (3) draw the token emitted if the walk ends at the node: the prefix of the piece masses (of the last child
+//       that moved the state, or of p) names the piece where the cumulative mass first exceeds u0 * total, and
+//       that piece finds the token by a block scan.
+// Two forms place this work.  Only the rows that the walk visits matter -- the root's and each kept child's --
+// but which they are is known only as the walk goes:
+//   * walk form: a workgroup per piece of every sequence.  The sequence's pieces take the walk's rows one after
+//     the other, deciding alike; only those rows are read.  Time grows with the walk's length.
+//     16 trees of 128 nodes x 152064 entries: 112 us, against 1.76 ms for every row's pieces in parallel (there
+//     the fp64 exponentials of 2048 rows bound the call; here the exponentials and loads of the visited rows,
+//     about 10 us a row, and the exchanges, about 1.7 us each).
+//   * row form: a workgroup per piece of every row of the tree, all at once; the sequence's last row to finish
+//     walks the decisions by ballots.  Time grows with the number of rows, not with the walk's length.  60 nodes x
+//     32000 entries: 24.5 us (28.6 with the statistics merged through a counter and a second round of loads, and
+//     butterfly reductions through LDS); a chain of exchanges as long as the widest node's children.
 // Probabilities are fp64, so that the integer outcome is decided in the precision of the definition; exp is
 // Tang's table-driven method.
 //
-// Forward progress.  A row piece only waits for the other pieces of its own row, which are consecutive
-// workgroups and wait for nothing outside the row; in the split form a workgroup only waits for rows whose
-// pieces all have smaller blockIdx.  Workgroups are dispatched in blockIdx order, so every wait ends.  Waits are nevertheless bounded (0.2 s by default), after which the results are unspecified and the
-// workspace's failure flag is set.  Nothing a wait that gave up leaves behind is used as a memory index (piece
-// and token positions are clamped, node indices come from the tree), and every arrival word still returns to
-// zero.
+// Exchange.  The pieces of a row (row form) or sequence (walk form) are a cluster.  In step s = 1, 2, ... (a row's
+// statistics, and in the walk form every child tested) every piece stores its few words, each 48 bits of data beside the step's number, to its own slot, and one wave
+// polls all slots of the cluster, lane k the slot of piece k, until every word carries the step's number: one
+// store and one load of latency, with no counter in between.  Slots alternate between two places: a piece
+// writes step s + 2 only after it has read every piece's step s + 1, which each wrote after reading step s.
+// A slot holds anything at entry; each piece clears its own and counts itself in on the cluster's counter, and
+// nobody reads a slot before that count is whole.  (A row of one piece has nothing to exchange.)  The row form
+// has slots for the statistics only: a child's residual mass is summed over the pieces by one atomic each, in
+// fixed point (units of 2^-51, so the sum does not depend on the order of arrival), with the arrivals above it
+// and the decision between them, and the pieces poll that word.
 //
-// Results cross workgroups through device-scope stores and loads, published before a relaxed device-scope
-// atomic on an arrival word (see kernels.h).  The walker of each sequence clears that sequence's arrival words,
-// so every one is back at zero when the launch ends.
+// Forward progress.  A piece waits only for the other pieces of its own cluster, which are consecutive
+// workgroups and wait for nothing outside it.  Workgroups are dispatched in blockIdx order and at most 64 make a
+// cluster, so every wait ends.  Waits are nevertheless bounded (0.2 s by default), after which the results are
+// unspecified and the workspace's failure flag is set: a piece whose wait gave up leaves, and the others' waits
+// for it end the same way.  Nothing that is read from a slot is used as a memory index, and every counter still
+// returns to zero.
+//
+// Slots, decisions and tokens cross workgroups through device-scope stores and loads (see kernels.h).
 #include "kernels.h"
 
 #include <limits.h>
@@ -54,23 +60,14 @@
 namespace dreams {
 namespace {
 
-constexpr int NT = kSampledThreads, NW = NT / 64;
-constexpr uint64_t kMassMask = (1ull << 53) - 1;   // accumulator: fixed-point mass in the low 53 bits,
-constexpr int kArrivalShift = 53;                  // arrivals above
-constexpr double kFixScale = 2251799813685248.0;   // 2^51 units per unit of mass
-constexpr double kFixUnit = 1.0 / kFixScale;
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ void store_d(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double load_d(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t load_u64(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+constexpr uint32_t kKeptBit = 1u << 15;  // a child's decision, beside the step's number (at most 2 * 128 steps)
+constexpr uint32_t kStepMask = kKeptBit - 1;
+constexpr int kArrivalShift = 53;                    // row form: a child's word: arrivals,
+constexpr uint64_t kKeptWordBit = 1ull << 52;        // decision, fixed-point mass
+constexpr double kFixScale = 2251799813685248.0, kFixUnit = 1.0 / kFixScale;   // 2^51 units per unit of mass
 
 // exp(x) for x <= 0, by Tang's table-driven method: x = k ln2/256 + r with k = round(x 256/ln2) and
 // |r| <= ln2/512 (ln2/256 split in two so that k times the high part is exact), e^x = 2^(k/256) e^r, with
@@ -92,103 +89,110 @@ __device__ __forceinline__ double scaled_exp(double d, double inv_tau, const dou
   return d == 0.0 ? 1.0 : exp_nonpos(d * inv_tau, tab);
 }
 
+__device__ __forceinline__ void store_d(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_d(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 struct Shared {
   double tab[256];                 // 2^(j/256)
-  double pm[kSampledMaxChunks];    // piece masses of the emitted token's distribution
-  double red_d[NW];
-  float red_f[NW];
-  int red_i[NW];
-  double scan[NW];
-  int flag, nsib, last_child, depth;
+  float wave_mt[16], wave_md[16];  // per wave: maxima and sums of a piece's statistics
+  double wave_st[16], wave_sd[16];
+  double wave_z[16];               // per wave: residual mass of a piece
+  double scan[16];
+  int pick[16], lastpos[16];
+  int nsib, flag, depth;
   int par[kMaxNodes];
   int sib[kMaxNodes];
   int path[kMaxNodes];
-  double zs[kMaxNodes];            // residual masses of earlier siblings (split form)
-  double st_c, st_d;               // a child's whole residual mass; the state (split form)
-  int st_slot;
+  double rs_mt, rs_ist, rs_md, rs_isd;   // the row's merged statistics
+  double st_z;                     // a child's whole residual mass ...
+  int st_kept, keep_here;          // ... and decision; the decision of this piece's own token
   int fin_piece;
   double fin_before, fin_thr;
   int gave_up;                     // a wait of this workgroup reached its bound
-  double rs_mt, rs_ist, rs_md, rs_isd;   // the row's merged statistics
 };
 
-// Block reductions: every lane reduces its wave by a butterfly, lane 0's value is kept, waves are combined in
-// wave order -- the same order on every call.
-__device__ __forceinline__ double block_sum(double v, Shared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  __syncthreads();
-  if (lane == 0) sh.red_d[wave] = v;
-  __syncthreads();
-  double s = sh.red_d[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) s += sh.red_d[w];
-  return s;
+// ---- wave reductions: within a row of 16 lanes by data-parallel moves (neighbours, pairs, mirrored halves), then
+// the four rows in order, read into scalars: the same value in every lane, the same order on every call
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false);
 }
-__device__ __forceinline__ float block_max(float v, Shared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  __syncthreads();
-  if (lane == 0) sh.red_f[wave] = v;
-  __syncthreads();
-  float m = sh.red_f[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) m = fmaxf(m, sh.red_f[w]);
-  return m;
+constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(float, dpp<CTRL>(__builtin_bit_cast(int, x)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)dpp<CTRL>((int)(uint32_t)u), hi = (uint32_t)dpp<CTRL>((int)(uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ float lane_of(float x, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+__device__ __forceinline__ double lane_of(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, dpp<kSwap1>(v));
+  v = fmaxf(v, dpp<kSwap2>(v));
+  v = fmaxf(v, dpp<kHalfMirror>(v));
+  v = fmaxf(v, dpp<kMirror>(v));
+  return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 16)), fmaxf(lane_of(v, 32), lane_of(v, 48)));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp<kSwap1>(v);
+  v += dpp<kSwap2>(v);
+  v += dpp<kHalfMirror>(v);
+  v += dpp<kMirror>(v);
+  return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
 }
 template <bool MAX>
-__device__ __forceinline__ int block_int(int v, Shared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const int o = __shfl_xor(v, off);
-    v = MAX ? max(v, o) : min(v, o);
-  }
-  __syncthreads();
-  if (lane == 0) sh.red_i[wave] = v;
-  __syncthreads();
-  int r = sh.red_i[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) r = MAX ? max(r, sh.red_i[w]) : min(r, sh.red_i[w]);
-  return r;
+__device__ __forceinline__ int wave_int(int v) {
+  auto pick = [](int x, int y) { return MAX ? max(x, y) : min(x, y); };
+  v = pick(v, dpp<kSwap1>(v));
+  v = pick(v, dpp<kSwap2>(v));
+  v = pick(v, dpp<kHalfMirror>(v));
+  v = pick(v, dpp<kMirror>(v));
+  return pick(pick(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+              pick(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
-// Exclusive prefix of v over the threads in thread order; `total` receives the sum over the block.
-__device__ __forceinline__ double block_exclusive_scan(double v, double& total, Shared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double inc = v;
+// inclusive prefix over the lanes
+__device__ __forceinline__ double wave_scan(double v) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    const double o = __shfl_up(inc, off);
-    if (lane >= off) inc += o;
+    const double o = __shfl_up(v, off);
+    if (lane >= off) v += o;
   }
-  __syncthreads();
-  if (lane == 63) sh.scan[wave] = inc;
-  __syncthreads();
-  double base = 0.0;
-  for (int w = 0; w < wave; ++w) base += sh.scan[w];
-  total = 0.0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) total += sh.scan[w];
-  return base + inc - v;
+  return v;
 }
 
-// A piece is SUB sub-pieces of NT * EPT entries.  In a sub-piece starting at x0, thread t holds entries
-// x0 + t * EPT + e (e < EPT); entries at or past x1 read as -inf.  (The split form's EPT; the row-piece form
-// holds kSampledPerThreadRow entries a thread.)
-constexpr int EPT = kSampledPerThread, SUBW = NT * EPT;
+// entries x0 + t * E + e (e < E) of a row for thread t; entries at or past x1 read as -inf
 template <bool VEC, int E>
-__device__ __forceinline__ void load_sub(const float* row, int x0, int x1, float (&v)[E]) {
+__device__ __forceinline__ void load_part(const float* row, int x0, int x1, float (&v)[E]) {
   const int base = x0 + (int)threadIdx.x * E;
-  if (VEC) {
+  if (VEC) {   // rows are 16-byte aligned and V a multiple of 4: a vector is wholly in or out
+    constexpr int W = E % 4 == 0 ? 4 : 2;
+    typedef float vec __attribute__((ext_vector_type(W)));
+    static_assert(E % W == 0, "whole vectors");
 #pragma unroll
-    for (int k = 0; k < E / 4; ++k) {
-      const int x = base + 4 * k;   // x0, x1 and x are multiples of 4: a vector is wholly in or out
-      f32x4 r = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-      if (x < x1) r = *(const f32x4*)(row + x);
+    for (int k = 0; k < E / W; ++k) {
+      const int x = base + W * k;
+      vec r;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * k + e] = r[e];
+      for (int e = 0; e < W; ++e) r[e] = -INFINITY;
+      if (x < x1) r = *(const vec*)(row + x);
+#pragma unroll
+      for (int e = 0; e < W; ++e) v[W * k + e] = r[e];
     }
   } else {
 #pragma unroll
@@ -196,159 +200,445 @@ __device__ __forceinline__ void load_sub(const float* row, int x0, int x1, float
   }
 }
 
-__device__ __forceinline__ uint64_t* acc_word(const SampledArgs& a, int b, int i) {
-  return (uint64_t*)(a.row_words + ((size_t)b * a.T + i) * a.row_stride);
-}
-__device__ __forceinline__ uint32_t* stats_word(const SampledArgs& a, int b, int i) {
-  return a.row_words + ((size_t)b * a.T + i) * a.row_stride + 2;
+// The children of node n in index order (sh.sib, sh.nsib), listed the same way by every piece; one wave.
+__device__ __forceinline__ void list_children(int n, int T, const int* par, Shared& sh) {
+  const int lane = threadIdx.x & 63;
+  const int k0 = lane, k1 = lane + 64;
+  const bool c0 = k0 > n && k0 < T && par[k0] == n;
+  const bool c1 = k1 > n && k1 < T && par[k1] == n;
+  const uint64_t b0 = __ballot(c0), b1 = __ballot(c1);
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  if (c0) sh.sib[__builtin_popcountll(b0 & below)] = k0;
+  if (c1) sh.sib[__builtin_popcountll(b0) + __builtin_popcountll(b1 & below)] = k1;
+  if (lane == 0) sh.nsib = __builtin_popcountll(b0) + __builtin_popcountll(b1);
 }
 
-// A row's maxima and normalisers from its pieces' statistics, merged in piece order by whichever workgroup
-// needs them (every one gets the same bits).
-struct RowStat {
-  double mt, inv_st, md, inv_sd;
-};
-__device__ RowStat merge_stats(const SampledArgs& a, size_t row, Shared& sh) {
-  const int tid = threadIdx.x;
-  const double* ps = a.piece_stat + row * a.chunks * 4;
-  if (a.chunks <= 64) {
-    // one wave, lane k holding piece k: all loads in one round trip, butterfly reductions (the same order in
-    // every workgroup)
-    if (tid < 64) {
+// Piece j of a cluster, one row at a time.  WALK: the cluster takes many rows.  HOLD: a one-part piece (NT * E entries) keeps p and q in registers;
+// else the piece's parts are streamed from memory in every pass over them.
+template <bool VEC, bool WALK, bool HOLD, int NT, int E>
+struct Piece {
+  static constexpr int PART = NT * E, NW = NT / 64;
+  // 64-bit words of a piece's slots, four each; the walk form's steps alternate between two
+  static constexpr int WORDS = 4, SLOTS = WALK ? 2 * WORDS : WORDS;
+  static_assert(SLOTS * 8 == (WALK ? kSampledWalkSlotBytes : kSampledRowSlotBytes), "slot layout");
+  const SampledArgs& a;
+  Shared& sh;
+  const int b, j;
+  uint32_t* const counter;        // the cluster's counter: pieces entered, then pieces left
+  uint64_t* const slots;          // [chunks][SLOTS]
+  uint32_t step = 0;
+  int n = 0;                      // the row's node
+  const float *trow = nullptr, *drow = nullptr;
+  float lt[E], ld[E];             // (HOLD) the piece's logits ...
+  double p[E], q[E];              // ... and probabilities
+  double mt, inv_st, md, inv_sd;  // the row's statistics
+  double C = 0.0, D = 1.0;        // the residual's state: max(p - C q, 0) / D
+  double mass = 0.0;              // wave 0, lane k: piece k's part of the state's mass ...
+  int src = -1;                   // ... unless it is that of child src (row form: stored by the pieces)
+
+  __device__ __forceinline__ Piece(const SampledArgs& args, Shared& s, int seq, int piece, uint32_t* ctr,
+                                   size_t cluster)
+      : a(args), sh(s), b(seq), j(piece), counter(ctr), slots(args.slots + cluster * args.chunks * SLOTS) {}
+
+  __device__ __forceinline__ bool wave0() const { return threadIdx.x < 64; }
+
+  // Clears this piece's slots and counts it in.
+  __device__ __forceinline__ void enter() {
+    if (wave0()) {
+      const int l = threadIdx.x;
+      if (l < SLOTS && a.chunks > 1) store_u64(slots + j * SLOTS + l, 0);
+      wait_vector_memory();
+      if (l == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  static __device__ __forceinline__ void store_u64(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // (wave 0) until ready() holds in every lane; false: the wait reached its bound
+  template <typename Ready>
+  __device__ __forceinline__ bool wait_until(Ready&& ready) {
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    while (true) {
+      if (__ballot(!ready()) == 0) return true;
+      if (__builtin_amdgcn_s_memrealtime() - t0 > a.wait_ticks) {
+        if (threadIdx.x == 0) {
+          raise_device_error(a.err, kErrWaitTimeout);
+          sh.gave_up = 1;
+        }
+        return false;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  // (wave 0) one step: lane w < N stores word w of this piece, 32 + 16 bits of data; on return lane k < chunks
+  // holds the words of piece k and, of the last one, the bit beside the step's number.
+  template <int N>
+  __device__ __forceinline__ bool exchange(uint32_t mine, uint32_t mine16, bool bit, uint32_t (&all)[N],
+                                           uint32_t (&all16)[N]) {
+    const int l = threadIdx.x;
+    ++step;
+    if (a.chunks == 1) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        all[k] = (uint32_t)__builtin_amdgcn_readlane((int)mine, k);
+        all16[k] = (uint32_t)__builtin_amdgcn_readlane((int)mine16, k);
+      }
+      return bit;
+    }
+    const int at = WALK && step % 2 == 0 ? WORDS : 0;
+    if (l < N)
+      store_u64(slots + j * SLOTS + at + l, ((uint64_t)mine << 32) | ((uint64_t)mine16 << 16) | step |
+                                                (l == N - 1 && bit ? kKeptBit : 0u));
+    if (step == 1)   // every piece has cleared its slots
+      wait_until([&] {
+        return __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)a.chunks;
+      });
+    const uint64_t* from = slots + min(l, a.chunks - 1) * SLOTS + at;
+    bool kept = false;
+    wait_until([&] {
+      uint64_t w[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) w[k] = __hip_atomic_load(from + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      bool now = true;
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        now = now && ((uint32_t)w[k] & kStepMask) == step;
+        all[k] = (uint32_t)(w[k] >> 32);
+        all16[k] = (uint32_t)(w[k] >> 16) & 0xffffu;
+      }
+      kept = ((uint32_t)w[N - 1] & kKeptBit) != 0;
+      return now;
+    });
+    return kept;
+  }
+  static __device__ __forceinline__ uint32_t low(double x) { return (uint32_t)__builtin_bit_cast(uint64_t, x); }
+  static __device__ __forceinline__ uint32_t high(double x) { return (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32); }
+  static __device__ __forceinline__ double from_words(uint32_t lo, uint32_t hi) {
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  }
+
+  __device__ __forceinline__ void load(int node) {
+    n = node;
+    const size_t row = (size_t)b * a.T + n;
+    trow = a.target_logits + row * a.V;
+    drow = a.draft_logits + row * a.V;
+    if (HOLD) {
+      const int x0 = j * PART;
+      load_part<VEC>(trow, x0, min(a.V, x0 + PART), lt);
+      load_part<VEC>(drow, x0, min(a.V, x0 + PART), ld);
+    }
+  }
+  // f(e, x, target logit, draft logit) for every entry x < V of the piece, in order
+  template <typename F>
+  __device__ __forceinline__ void entries(F&& f) {
+    const int tid = threadIdx.x, V = a.V;
+    if (HOLD) {
+      const int base = j * PART + tid * E;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (base + e < V) f(e, base + e, lt[e], ld[e]);
+    } else {
+#pragma unroll 1
+      for (int sp = 0; sp < a.sub_pieces; ++sp) {
+        const long long at = ((long long)j * a.sub_pieces + sp) * PART;
+        if (at >= V) break;
+        const int x0 = (int)at, x1 = (int)min((long long)V, at + PART);
+        float ta[E], da[E];
+        load_part<VEC>(trow, x0, x1, ta);
+        load_part<VEC>(drow, x0, x1, da);
+        const int base = x0 + tid * E;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (base + e < V) f(e, base + e, ta[e], da[e]);
+      }
+    }
+  }
+  __device__ __forceinline__ double prob_p(float t) {
+    return scaled_exp((double)t - mt, a.inv_tau, sh.tab) * inv_st;
+  }
+  __device__ __forceinline__ double prob_q(float d) {
+    return scaled_exp((double)d - md, a.inv_tau, sh.tab) * inv_sd;
+  }
+
+  // (wave 0) sums relative to their own maxima, one pair a lane (no pair: -inf, 0), merged: the largest maximum,
+  // and the sum relative to it
+  __device__ __forceinline__ void merge(float& m, double& s) {
+    const float top = wave_max(m);
+    s = s != 0.0 ? s * scaled_exp((double)m - (double)top, a.inv_tau, sh.tab) : 0.0;
+    s = wave_sum(s);
+    m = top;
+  }
+
+  // The row's statistics: maxima and sums of exp((l - max) / tau), target and draft, of every wave, of the piece,
+  // and of the row, and from them p and q of the piece's entries.  A one-part piece keeps its exponentials
+  // relative to its wave's maxima, from which p and q follow by one factor; a streamed piece re-references each
+  // thread's sums when a maximum grows.
+  __device__ __forceinline__ void statistics() {
+    const int tid = threadIdx.x, V = a.V, wave = tid >> 6;
+    float wt = -INFINITY, wd = -INFINITY;
+    double st = 0.0, sd = 0.0;
+    if (HOLD) {
+      const int base = j * PART + tid * E;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {   // (entries past the vocabulary read as -inf)
+        wt = fmaxf(wt, lt[e]);
+        wd = fmaxf(wd, ld[e]);
+      }
+      wt = wave_max(wt);
+      wd = wave_max(wd);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const bool in = base + e < V;
+        p[e] = in ? scaled_exp((double)lt[e] - (double)wt, a.inv_tau, sh.tab) : 0.0;
+        q[e] = in ? scaled_exp((double)ld[e] - (double)wd, a.inv_tau, sh.tab) : 0.0;
+        st += p[e];
+        sd += q[e];
+      }
+      st = wave_sum(st);
+      sd = wave_sum(sd);
+    } else {
+      entries([&](int, int, float t, float d) {
+        if (t > wt) {
+          if (st != 0.0) st *= scaled_exp((double)wt - (double)t, a.inv_tau, sh.tab);
+          wt = t;
+        }
+        if (d > wd) {
+          if (sd != 0.0) sd *= scaled_exp((double)wd - (double)d, a.inv_tau, sh.tab);
+          wd = d;
+        }
+        st += scaled_exp((double)t - (double)wt, a.inv_tau, sh.tab);
+        sd += scaled_exp((double)d - (double)wd, a.inv_tau, sh.tab);
+      });
+      merge(wt, st);
+      merge(wd, sd);
+    }
+    if ((tid & 63) == 0) {
+      sh.wave_mt[wave] = wt;
+      sh.wave_md[wave] = wd;
+      sh.wave_st[wave] = st;
+      sh.wave_sd[wave] = sd;
+    }
+    __syncthreads();
+    if (wave0()) {
+      float m1 = tid < NW ? sh.wave_mt[tid % NW] : -INFINITY, m2 = tid < NW ? sh.wave_md[tid % NW] : -INFINITY;
+      double s1 = tid < NW ? sh.wave_st[tid % NW] : 0.0, s2 = tid < NW ? sh.wave_sd[tid % NW] : 0.0;
+      merge(m1, s1);
+      merge(m2, s2);
+      const uint32_t mine = tid == 0   ? __builtin_bit_cast(uint32_t, m1)
+                            : tid == 1 ? __builtin_bit_cast(uint32_t, m2)
+                            : tid == 2 ? low(s1)
+                                       : high(s1);
+      const uint32_t mine16 = ((tid < 2 ? low(s2) : high(s2)) >> (tid & 1 ? 16 : 0)) & 0xffffu;
+      uint32_t w[4], h[4];
+      exchange<4>(mine, mine16, false, w, h);
       const bool in = tid < a.chunks;
-      const double v0 = in ? load_d(ps + 4 * tid + 0) : -INFINITY, v1 = in ? load_d(ps + 4 * tid + 1) : 0.0;
-      const double v2 = in ? load_d(ps + 4 * tid + 2) : -INFINITY, v3 = in ? load_d(ps + 4 * tid + 3) : 0.0;
-      float mt = (float)v0, md = (float)v2;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        mt = fmaxf(mt, __shfl_xor(mt, off));
-        md = fmaxf(md, __shfl_xor(md, off));
-      }
-      double st = in ? v1 * scaled_exp(v0 - (double)mt, a.inv_tau, sh.tab) : 0.0;
-      double sd = in ? v3 * scaled_exp(v2 - (double)md, a.inv_tau, sh.tab) : 0.0;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        st += __shfl_xor(st, off);
-        sd += __shfl_xor(sd, off);
-      }
+      m1 = in ? __builtin_bit_cast(float, w[0]) : -INFINITY;
+      m2 = in ? __builtin_bit_cast(float, w[1]) : -INFINITY;
+      s1 = in ? from_words(w[2], w[3]) : 0.0;
+      s2 = in ? from_words(h[0] | h[1] << 16, h[2] | h[3] << 16) : 0.0;
+      const float own = m1;
+      mass = s1;
+      merge(m1, s1);
+      merge(m2, s2);
+      const double ist = 1.0 / s1;
+      // piece k's share of the target's own distribution
+      mass = in ? mass * scaled_exp((double)own - (double)m1, a.inv_tau, sh.tab) * ist : 0.0;
       if (tid == 0) {
-        sh.rs_mt = mt;
-        sh.rs_ist = 1.0 / st;
-        sh.rs_md = md;
-        sh.rs_isd = 1.0 / sd;
+        sh.rs_mt = m1;
+        sh.rs_ist = ist;
+        sh.rs_md = m2;
+        sh.rs_isd = 1.0 / s2;
       }
     }
     __syncthreads();
-    return RowStat{sh.rs_mt, sh.rs_ist, sh.rs_md, sh.rs_isd};
+    mt = sh.rs_mt;
+    inv_st = sh.rs_ist;
+    md = sh.rs_md;
+    inv_sd = sh.rs_isd;
+    if (HOLD) {
+      const double ft = wt == -INFINITY ? 0.0 : scaled_exp((double)wt - mt, a.inv_tau, sh.tab) * inv_st;
+      const double fd = wd == -INFINITY ? 0.0 : scaled_exp((double)wd - md, a.inv_tau, sh.tab) * inv_sd;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        p[e] *= ft;
+        q[e] *= fd;
+      }
+    }
+    C = 0.0;
+    D = 1.0;
+    src = -1;
   }
-  float mt = -INFINITY, md = -INFINITY;
-  for (int k = tid; k < a.chunks; k += NT) {
-    mt = fmaxf(mt, (float)load_d(ps + 4 * k + 0));
-    md = fmaxf(md, (float)load_d(ps + 4 * k + 2));
-  }
-  mt = block_max(mt, sh);
-  md = block_max(md, sh);
-  double st = 0.0, sd = 0.0;
-  for (int k = tid; k < a.chunks; k += NT) {
-    st += load_d(ps + 4 * k + 1) * scaled_exp(load_d(ps + 4 * k + 0) - (double)mt, a.inv_tau, sh.tab);
-    sd += load_d(ps + 4 * k + 3) * scaled_exp(load_d(ps + 4 * k + 2) - (double)md, a.inv_tau, sh.tab);
-  }
-  st = block_sum(st, sh);
-  sd = block_sum(sd, sh);
-  return RowStat{mt, 1.0 / st, md, 1.0 / sd};
-}
 
-// The token emitted if the walk ends at node n with residual max(p - C q, 0): its piece masses are those of
-// child `src`'s residual, or, for src < 0, the target's own (from n's piece statistics).  Stored to
-// final_token by thread 0 (every thread then waits for its stores).
-template <bool VEC, int SUB>
-__device__ void final_draw(const SampledArgs& a, int b, int n, const RowStat& rs, double C, int src, Shared& sh) {
-  const int tid = threadIdx.x, T = a.T, V = a.V;
-  const size_t row = (size_t)b * T + n;
-  if (src >= 0) {
-    const double* m = a.mass + ((size_t)b * T + src) * a.chunks;
-    for (int k = tid; k < a.chunks; k += NT) sh.pm[k] = load_d(m + k);
-  } else {
-    const double* ps = a.piece_stat + row * a.chunks * 4;
-    for (int k = tid; k < a.chunks; k += NT)
-      sh.pm[k] = load_d(ps + 4 * k + 1) * scaled_exp(load_d(ps + 4 * k + 0) - rs.mt, a.inv_tau, sh.tab) * rs.inv_st;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double total = 0.0;
-    for (int k = 0; k < a.chunks; ++k) total += sh.pm[k];
-    const double thr = (double)a.uniforms[(size_t)b * T] * total;
-    double cum = 0.0, before = 0.0, pos_before = 0.0;
-    int piece = -1, pos_piece = 0;
-    for (int k = 0; k < a.chunks; ++k) {
-      const double mk = sh.pm[k];
-      if (mk > 0.0) {
-        pos_piece = k;
-        pos_before = cum;
+  // Child c (token x) of the row's node, tested against the state (C, D) its earlier siblings left, by the piece
+  // that holds x; its residual mass is summed over the pieces.  Moves the state past the child.  True if c is
+  // kept; the row form stores the decision (for the walk).  last: no child of the node follows.
+  __device__ __forceinline__ bool test_child(int c, bool last) {
+    const int tid = threadIdx.x, V = a.V, wave = tid >> 6;
+    const size_t rb = (size_t)b * a.T;
+    const int x = a.tokens[rb + c];
+    const double CC = C + D;
+    double z = 0.0, px = 0.0, qx = 0.0;
+    bool holds = false;
+    entries([&](int e, int xi, float t, float d) {
+      const double pe = HOLD ? p[e] : prob_p(t), qe = HOLD ? q[e] : prob_q(d);
+      z += fmax(pe - CC * qe, 0.0);
+      if (xi == x) {
+        px = pe;
+        qx = qe;
+        holds = true;
       }
-      if (cum + mk > thr) {
-        piece = k;
-        before = cum;
-        break;
+    });
+    // c's decision, by the thread holding its token (a token outside the vocabulary is never kept)
+    if (holds) {
+      const int keep = ((double)a.uniforms[rb + c] * qx) * D < fmax(px - C * qx, 0.0);
+      if (!WALK) store_coherent(a.kept + rb + c, (int32_t)keep);
+      sh.keep_here = keep;
+    }
+    if (!WALK && (x < 0 || x >= V) && j == 0 && tid == 0) store_coherent(a.kept + rb + c, 0);
+    z = wave_sum(z);
+    if ((tid & 63) == 0) sh.wave_z[wave] = z;
+    __syncthreads();
+    double part = mass;
+    if (wave0()) {
+      z = wave_sum(tid < NW ? sh.wave_z[tid % NW] : 0.0);
+      const bool keep = sh.keep_here != 0;
+      bool kept;
+      if (WALK || a.chunks == 1) {
+        uint32_t w[2], h[2];
+        kept = exchange<2>(tid == 0 ? low(z) : high(z), 0, keep, w, h);
+        kept = __ballot(kept && tid < a.chunks) != 0;
+        part = tid < a.chunks ? from_words(w[0], w[1]) : 0.0;
+        z = wave_sum(part);
+      } else {
+        if (tid == 0) store_d(a.mass + (rb + c) * a.chunks + j, z);
+        if (last) wait_vector_memory();   // (the piece's masses are stored before its last arrival)
+        // A piece's mass is at most 1 (up to rounding), a row's below 2, so that the decision's bit is free; after
+        // a wait gave up it is meaningless and counts as 0, so that it can never carry into the arrivals.
+        const double zc = sh.gave_up ? 0.0 : fmin(fmax(z, 0.0), 2.0);
+        const uint64_t add = (1ull << kArrivalShift) + (uint64_t)rint(zc * kFixScale) + (keep ? kKeptWordBit : 0);
+        uint64_t* word = (uint64_t*)(a.row_ctr + (rb + c) * a.row_stride);
+        if (tid == 0) __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t v = 0;
+        wait_until([&] {
+          v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          return (int)(v >> kArrivalShift) == a.chunks;
+        });
+        kept = (v & kKeptWordBit) != 0;
+        z = (double)(v & (kKeptWordBit - 1)) * kFixUnit;
       }
-      cum += mk;
+      if (tid == 0) {
+        sh.keep_here = 0;
+        sh.st_z = z;
+        sh.st_kept = kept;
+      }
     }
-    if (piece < 0) {   // no crossing (an all-zero residual): the last piece of positive mass
-      piece = pos_piece;
-      before = pos_before;
+    __syncthreads();
+    if (sh.st_z > 0.0) {
+      C = CC;
+      D = sh.st_z;
+      mass = part;
+      src = c;
     }
-    sh.fin_piece = piece;
-    sh.fin_before = before;
-    sh.fin_thr = thr;
+    return sh.st_kept;
   }
-  __syncthreads();
-  const int piece = sh.fin_piece;
-  const double thr = sh.fin_thr;
-  double before = sh.fin_before;
-  const float* trow = a.target_logits + row * V;
-  const float* drow = a.draft_logits + row * V;
-  int pick = INT_MAX, last_pos = -1;
+
+  // The token drawn if the walk ends at the row's node: the piece where the masses cross u0 times their total
+  // (found alike by every piece) takes the prefix of r = max(p - C q, 0) over its entries, part by part.  -1 in
+  // every other piece; the same in every thread.
+  __device__ __forceinline__ int draw() {
+    const int tid = threadIdx.x, V = a.V, wave = tid >> 6;
+    if (wave0()) {
+      if (!WALK && src >= 0 && a.chunks > 1)
+        mass = tid < a.chunks ? load_d(a.mass + ((size_t)b * a.T + src) * a.chunks + tid) : 0.0;
+      const double inc = wave_scan(mass);
+      const double thr = (double)a.uniforms[(size_t)b * a.T] * lane_of(inc, 63);
+      const uint64_t over = __ballot(inc > thr), some = __ballot(mass > 0.0);
+      // (no crossing -- an all-zero residual: the last piece of positive mass)
+      const int piece = over ? __builtin_ctzll(over) : some ? 63 - __builtin_clzll(some) : 0;
+      const double before = piece > 0 ? lane_of(inc, piece - 1) : 0.0;
+      if (tid == 0) {
+        sh.fin_piece = piece;
+        sh.fin_before = before;
+        sh.fin_thr = thr;
+      }
+    }
+    __syncthreads();
+    if (sh.fin_piece != j) return -1;
+    const double thr = sh.fin_thr;
+    double before = sh.fin_before;
+    int pick = INT_MAX, last_pos = -1;
+    const int parts = HOLD ? 1 : a.sub_pieces;
+    const long long first = (long long)j * parts * PART;
 #pragma unroll 1
-  for (int sp = 0; sp < SUB && pick == INT_MAX; ++sp) {
-    const int x0 = (piece * SUB + sp) * SUBW, x1 = min(V, x0 + SUBW);
-    if (x0 >= V) break;
-    float lt[EPT], ld[EPT];
-    load_sub<VEC>(trow, x0, x1, lt);
-    load_sub<VEC>(drow, x0, x1, ld);
-    const int base = x0 + tid * EPT;
-    double r[EPT], mine = 0.0;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      r[e] = 0.0;
-      if (base + e < x1) {
-        const double p = scaled_exp((double)lt[e] - rs.mt, a.inv_tau, sh.tab) * rs.inv_st;
-        const double q = C == 0.0 ? 0.0 : scaled_exp((double)ld[e] - rs.md, a.inv_tau, sh.tab) * rs.inv_sd;
-        r[e] = fmax(p - C * q, 0.0);
+    for (int sp = 0; sp < parts && pick == INT_MAX; ++sp) {
+      const long long at = first + (long long)sp * PART;
+      if (at >= V) break;
+      const int x0 = (int)at, x1 = (int)min((long long)V, at + PART), base = x0 + tid * E;
+      float ta[E], da[E];
+      if (!HOLD) {
+        load_part<VEC>(trow, x0, x1, ta);
+        load_part<VEC>(drow, x0, x1, da);
       }
-      mine += r[e];
-    }
-    double total;
-    double cum = before + block_exclusive_scan(mine, total, sh);
-    int pk = INT_MAX, lp = -1;
+      double r[E], own = 0.0;
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      cum += r[e];
-      if (pk == INT_MAX && cum > thr) pk = base + e;
-      if (r[e] > 0.0) lp = base + e;
+      for (int e = 0; e < E; ++e) {
+        r[e] = 0.0;
+        if (base + e < V) {
+          const double pe = HOLD ? p[e] : prob_p(ta[e]);
+          const double qe = C == 0.0 ? 0.0 : (HOLD ? q[e] : prob_q(da[e]));
+          r[e] = fmax(pe - C * qe, 0.0);
+        }
+        own += r[e];
+      }
+      // the entries before this thread's, over the block in thread order
+      const double inc = wave_scan(own);
+      if ((tid & 63) == 63) sh.scan[wave] = inc;
+      __syncthreads();
+      double cum = before + (inc - own), total = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const double s = sh.scan[w];
+        if (w < wave) cum += s;
+        total += s;
+      }
+      int pk = INT_MAX, lp = -1;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        cum += r[e];
+        if (pk == INT_MAX && cum > thr) pk = base + e;
+        if (r[e] > 0.0) lp = base + e;
+      }
+      pk = wave_int<false>(pk);
+      lp = wave_int<true>(lp);
+      if ((tid & 63) == 0) {
+        sh.pick[wave] = pk;
+        sh.lastpos[wave] = lp;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        pick = min(pick, sh.pick[w]);
+        last_pos = max(last_pos, sh.lastpos[w]);
+      }
+      before += total;
+      __syncthreads();
     }
-    pick = block_int<false>(pk, sh);
-    last_pos = max(last_pos, block_int<true>(lp, sh));
-    before += total;
+    // (rounding between the piece masses and this prefix can leave the crossing just outside the piece: then
+    // the piece's last entry of positive mass)
+    if (pick == INT_MAX) pick = last_pos >= 0 ? last_pos : (int)min((long long)V - 1, first);
+    return pick;
   }
-  // (rounding between the piece masses and this prefix can leave the crossing just outside the piece: then
-  // the piece's last entry of positive mass)
-  if (pick == INT_MAX) pick = last_pos >= 0 ? last_pos : min(V - 1, piece * SUB * SUBW);
-  if (tid == 0) store_coherent(a.final_token + row, pick);
-  wait_vector_memory();
-}
 
-// ---------------------------------------------------------------------------------------------------- walk
-__device__ void walk(const SampledArgs& a, int b, Shared& sh) {
+  // (thread 0, once this piece's stores are done) counts this piece out; true in the cluster's last one
+  __device__ __forceinline__ bool leave() {
+    return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (uint32_t)(2 * a.chunks - 1);
+  }
+};
+
+// ---------------------------------------------------------------------------------------------- row form
+// The walk over every node's decisions and prepared token, by the sequence's last row to finish.
+__device__ void walk_decisions(const SampledArgs& a, int b, Shared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int T = a.T;
   const size_t rb = (size_t)b * T;
@@ -382,640 +672,113 @@ __device__ void walk(const SampledArgs& a, int b, Shared& sh) {
   const int depth = sh.depth;
   if (tid < T) {
     a.accept_path[rb + tid] = tid <= depth ? sh.path[tid] : -1;
-    __hip_atomic_store(acc_word(a, b, tid), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    reset_counter(stats_word(a, b, tid));
+    uint32_t* words = a.row_ctr + (rb + tid) * a.row_stride;
+    __hip_atomic_store((uint64_t*)words, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    reset_counter(words + kSampledRowCounter);
   }
 }
 
-// ------------------------------------------------------------- split form (pieces of many sub-pieces)
-// Arrival of a finished row at its sequence; the sequence's last row runs the walk.
-__device__ __forceinline__ void row_done(const SampledArgs& a, int b, Shared& sh) {
-  __syncthreads();   // every thread has read the previous flag
-  if (threadIdx.x == 0)
-    sh.flag = __hip_atomic_fetch_add(a.seq_ctr + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-              (uint32_t)(2 * a.T - 2);
-  __syncthreads();
-  if (sh.flag) walk(a, b, sh);
-}
-
-// ------------------------------------------------------------------------------------------ stats pieces
-template <bool VEC, int SUB>
-__device__ void stats_piece(const SampledArgs& a, int b, int i, int j, Shared& sh) {
-  const int tid = threadIdx.x;
-  const size_t row = (size_t)b * a.T + i;
-  const float* trow = a.target_logits + row * a.V;
-  const float* drow = a.draft_logits + row * a.V;
-  // per thread: running maxima and sums relative to them (rescaled when a maximum grows)
-  float mt = -INFINITY, md = -INFINITY;
-  double st = 0.0, sd = 0.0;
-  float lt[EPT], ld[EPT], nt[EPT], nd[EPT];
-  int x0 = j * SUB * SUBW;
-  load_sub<VEC>(trow, x0, min(a.V, x0 + SUBW), lt);
-  load_sub<VEC>(drow, x0, min(a.V, x0 + SUBW), ld);
-#pragma unroll 1
-  for (int sp = 0; sp < SUB; ++sp, x0 += SUBW) {
-    if (sp + 1 < SUB) {   // the next sub-piece's loads in flight during this one's arithmetic
-      const int y0 = x0 + SUBW;
-      load_sub<VEC>(trow, y0, min(a.V, y0 + SUBW), nt);
-      load_sub<VEC>(drow, y0, min(a.V, y0 + SUBW), nd);
-    }
-    float ct = -INFINITY, cd = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      ct = fmaxf(ct, lt[e]);
-      cd = fmaxf(cd, ld[e]);
-    }
-    if (ct > mt) {
-      if (st != 0.0) st *= scaled_exp((double)mt - (double)ct, a.inv_tau, sh.tab);
-      mt = ct;
-    }
-    if (cd > md) {
-      if (sd != 0.0) sd *= scaled_exp((double)md - (double)cd, a.inv_tau, sh.tab);
-      md = cd;
-    }
-    const int base = x0 + tid * EPT, x1 = min(a.V, x0 + SUBW);
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if (base + e < x1) {
-        st += scaled_exp((double)lt[e] - (double)mt, a.inv_tau, sh.tab);
-        sd += scaled_exp((double)ld[e] - (double)md, a.inv_tau, sh.tab);
-      }
-    if (sp + 1 < SUB) {
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        lt[e] = nt[e];
-        ld[e] = nd[e];
-      }
-    }
-  }
-  const float bt = block_max(mt, sh), bd = block_max(md, sh);
-  if (st != 0.0) st *= scaled_exp((double)mt - (double)bt, a.inv_tau, sh.tab);
-  if (sd != 0.0) sd *= scaled_exp((double)md - (double)bd, a.inv_tau, sh.tab);
-  mt = bt;
-  md = bd;
-  st = block_sum(st, sh);
-  sd = block_sum(sd, sh);
-  uint32_t* w = stats_word(a, b, i);
-  if (tid == 0) {
-    double* ps = a.piece_stat + (row * a.chunks + j) * 4;
-    store_d(ps + 0, mt);
-    store_d(ps + 1, st);
-    store_d(ps + 2, md);
-    store_d(ps + 3, sd);
-    wait_vector_memory();
-    sh.flag = arrive_last(w, (uint32_t)a.chunks);
-  }
-  __syncthreads();
-  if (!sh.flag) return;
-
-  // the row's last piece: at a leaf, the token emitted if the walk ends here (the target's own distribution)
-  const int T = a.T;
-  const bool child = tid > i && tid < T && a.parent[(size_t)b * T + tid] == i;
-  if (!__syncthreads_or(child)) {
-    const RowStat rs = merge_stats(a, row, sh);
-    final_draw<VEC, SUB>(a, b, i, rs, 0.0, -1, sh);
-  }
-  row_done(a, b, sh);
-}
-
-// ------------------------------------------------------------------------------------------- pass pieces
-template <bool VEC, int SUB>
-__device__ void pass_piece(const SampledArgs& a, int b, int c, int j, Shared& sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int T = a.T;
+// Workgroup (b, n, j): piece j of row n.
+template <bool VEC, int NT, int E>
+__global__ __launch_bounds__(NT) void tree_accept_sampled_rows_kernel(SampledArgs a) {
+  __shared__ Shared sh;
+  const int tid = threadIdx.x, T = a.T;
+  const int j = (int)(blockIdx.x % (unsigned)a.chunks), row = (int)(blockIdx.x / (unsigned)a.chunks);
+  const int b = row / T, n = row - b * T;
   const size_t rb = (size_t)b * T;
-  if (tid < T) sh.par[tid] = a.parent[rb + tid];
-  if (tid == 0) sh.gave_up = 0;
+  Piece<VEC, false, true, NT, E> pc(a, sh, b, j, a.row_ctr + (size_t)row * a.row_stride + kSampledRowCounter, row);
+  pc.enter();
+  pc.load(n);
+  if (tid < 256) sh.tab[tid] = exp2((double)tid * (1.0 / 256.0));
+  if (tid < 64) list_children(n, T, a.parent + rb, sh);
+  if (tid == 0) sh.gave_up = sh.keep_here = 0;
   __syncthreads();
-  const int n = sh.par[c];
-  const bool valid = n >= 0 && n < c;
-  const int x = a.tokens[rb + c];
-  double z = 0.0, C = 0.0, D = 1.0, CC = 1.0;
-  int src = -1;
-  RowStat rs{};
-  if (valid) {
-    const size_t row = rb + n;
-    const float* trow = a.target_logits + row * a.V;
-    const float* drow = a.draft_logits + row * a.V;
-    // one-sub-piece pieces: loaded now, p and q computed while the earlier siblings may still be running;
-    // larger pieces (where throughput matters more than the wait chain) are streamed after the waits
-    constexpr bool HOLD = SUB == 1;
-    const int x0 = j * SUB * SUBW, x1 = min(a.V, x0 + SUBW);
-    float lt[EPT], ld[EPT];
-    if (HOLD) {
-      load_sub<VEC>(trow, x0, x1, lt);
-      load_sub<VEC>(drow, x0, x1, ld);
-    }
-    // c's earlier siblings (in index order) and whether c is n's last child
-    if (wave == 0) {
-      const int k0 = lane, k1 = lane + 64;
-      const bool s0 = k0 > n && k0 < c && sh.par[k0] == n;
-      const bool s1 = k1 > n && k1 < c && k1 < T && sh.par[k1] == n;
-      const bool l0 = k0 > c && k0 < T && sh.par[k0] == n;
-      const bool l1 = k1 > c && k1 < T && sh.par[k1] == n;
-      const uint64_t b0 = __ballot(s0), b1 = __ballot(s1);
-      const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-      if (s0) sh.sib[__builtin_popcountll(b0 & below)] = k0;
-      if (s1) sh.sib[__builtin_popcountll(b0) + __builtin_popcountll(b1 & below)] = k1;
-      const bool later = (__ballot(l0) | __ballot(l1)) != 0;
-      if (lane == 0) {
-        sh.nsib = __builtin_popcountll(b0) + __builtin_popcountll(b1);
-        sh.last_child = !later;
-      }
-      // every piece of n's statistics
-      if (lane == 0) {
-        const uint32_t* w = stats_word(a, b, n);
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-        while (__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)a.chunks) {
-          if (__builtin_amdgcn_s_memrealtime() - t0 > a.wait_ticks) {
-            raise_device_error(a.err, kErrWaitTimeout);
-            sh.gave_up = 1;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(2);
-        }
-      }
-    }
-    __syncthreads();
-    rs = merge_stats(a, row, sh);
-    double p[EPT], q[EPT];
-    if (HOLD) {
-      const int base = x0 + tid * EPT;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const bool in = base + e < x1;
-        p[e] = in ? scaled_exp((double)lt[e] - rs.mt, a.inv_tau, sh.tab) * rs.inv_st : 0.0;
-        q[e] = in ? scaled_exp((double)ld[e] - rs.md, a.inv_tau, sh.tab) * rs.inv_sd : 0.0;
-      }
-    }
-    // the earlier siblings' residual masses: complete once their accumulators count every piece
-    const int nsib = sh.nsib;
-    if (wave == 0 && nsib > 0) {
-      const uint64_t* w0 = lane < nsib ? acc_word(a, b, sh.sib[lane]) : nullptr;
-      const uint64_t* w1 = lane + 64 < nsib ? acc_word(a, b, sh.sib[lane + 64]) : nullptr;
-      uint64_t v0 = 0, v1 = 0;
-      const uint64_t full = (uint64_t)a.chunks << kArrivalShift;
-      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      while (true) {
-        if (w0) v0 = load_u64(w0);
-        if (w1) v1 = load_u64(w1);
-        const bool done = (!w0 || (v0 & ~kMassMask) == full) && (!w1 || (v1 & ~kMassMask) == full);
-        if (__ballot(!done) == 0) break;
-        if (__builtin_amdgcn_s_memrealtime() - t0 > a.wait_ticks) {
-          if (lane == 0) {
-            raise_device_error(a.err, kErrWaitTimeout);
-            sh.gave_up = 1;
-          }
-          break;
-        }
-        __builtin_amdgcn_s_sleep(2);
-      }
-      if (w0) sh.zs[lane] = (double)(v0 & kMassMask) * kFixUnit;
-      if (w1) sh.zs[lane + 64] = (double)(v1 & kMassMask) * kFixUnit;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double c_run = 0.0, d_run = 1.0;
-      int s_run = -1;
-      for (int k = 0; k < nsib; ++k) {
-        const double zk = sh.zs[k];
-        if (zk > 0.0) {
-          c_run += d_run;
-          d_run = zk;
-          s_run = sh.sib[k];
-        }
-      }
-      sh.st_c = c_run;
-      sh.st_d = d_run;
-      sh.st_slot = s_run;
-    }
-    __syncthreads();
-    C = sh.st_c;
-    D = sh.st_d;
-    src = sh.st_slot;
-    CC = C + D;
-    double px = 0.0, qx = 0.0;
-    bool mine = false;
-    if (HOLD) {
-      const int base = x0 + tid * EPT;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        z += fmax(p[e] - CC * q[e], 0.0);
-        if (base + e == x && base + e < x1) {
-          px = p[e];
-          qx = q[e];
-          mine = true;
-        }
-      }
-    } else {
-      float nt[EPT], nd[EPT];
-      int y0 = x0;
-      load_sub<VEC>(trow, y0, min(a.V, y0 + SUBW), lt);
-      load_sub<VEC>(drow, y0, min(a.V, y0 + SUBW), ld);
-#pragma unroll 1
-      for (int sp = 0; sp < SUB; ++sp, y0 += SUBW) {
-        if (sp + 1 < SUB) {   // the next sub-piece's loads in flight during this one's arithmetic
-          load_sub<VEC>(trow, y0 + SUBW, min(a.V, y0 + 2 * SUBW), nt);
-          load_sub<VEC>(drow, y0 + SUBW, min(a.V, y0 + 2 * SUBW), nd);
-        }
-        const int base = y0 + tid * EPT, y1 = min(a.V, y0 + SUBW);
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          if (base + e < y1) {
-            const double pe = scaled_exp((double)lt[e] - rs.mt, a.inv_tau, sh.tab) * rs.inv_st;
-            const double qe = scaled_exp((double)ld[e] - rs.md, a.inv_tau, sh.tab) * rs.inv_sd;
-            z += fmax(pe - CC * qe, 0.0);
-            if (base + e == x) {
-              px = pe;
-              qx = qe;
-              mine = true;
-            }
-          }
-        }
-        if (sp + 1 < SUB) {
-#pragma unroll
-          for (int e = 0; e < EPT; ++e) {
-            lt[e] = nt[e];
-            ld[e] = nd[e];
-          }
-        }
-      }
-    }
-    // c's decision, by the thread holding its token
-    if (mine) store_coherent(a.kept + rb + c, (int32_t)(((double)a.uniforms[rb + c] * qx) * D < fmax(px - C * qx, 0.0)));
-  }
-  if ((!valid || x < 0 || x >= a.V) && j == 0 && tid == 0) store_coherent(a.kept + rb + c, 0);
-  z = block_sum(z, sh);
-  if (tid == 0) store_d(a.mass + (rb + c) * a.chunks + j, z);
-  wait_vector_memory();
-  __syncthreads();
-  if (tid == 0) {
-    // A piece's mass is at most 1 (up to rounding); after a wait gave up it is meaningless and counts as 0, so
-    // that it can never carry into the arrival bits: the count, and with it the walk, still completes.
-    const double zc = sh.gave_up ? 0.0 : fmin(fmax(z, 0.0), 2.0);
-    const uint64_t mine = (uint64_t)rint(zc * kFixScale);
-    const uint64_t old = __hip_atomic_fetch_add(acc_word(a, b, c), (1ull << kArrivalShift) + mine, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    sh.flag = (int)(old >> kArrivalShift) == a.chunks - 1;
-    sh.zs[0] = (double)((old & kMassMask) + mine) * kFixUnit;   // the row's whole residual mass
-  }
-  __syncthreads();
-  if (!sh.flag) return;
-  // c's last piece: if c is n's last child, the token emitted if the walk ends at n (every child rejected)
-  if (valid && sh.last_child) {
-    const bool moved = sh.zs[0] > 0.0;
-    final_draw<VEC, SUB>(a, b, n, rs, moved ? CC : C, moved ? c : src, sh);
-    __syncthreads();
-  }
-  row_done(a, b, sh);
-}
-
-// ------------------------------------------------------------------------------------------- row pieces
-// Workgroup (b, n, j): piece j of row n.  Its logits stay in registers for the whole call.
-template <bool VEC, int SUB, int E>
-__device__ void row_piece(const SampledArgs& a, int b, int n, int j, Shared& sh) {
-  constexpr int EPT = E, SUBW = NT * E;   // (this form's entries per thread and per sub-piece)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int T = a.T, V = a.V;
-  const size_t rb = (size_t)b * T, row = rb + n;
-  const float* trow = a.target_logits + row * V;
-  const float* drow = a.draft_logits + row * V;
-  // One-part pieces keep their logits (and later p and q) in registers; four-part pieces stream their parts
-  // from memory in every pass (the registers would not hold them).
-  constexpr bool HOLD = SUB == 1;
-  float lt0[EPT], ld0[EPT];
-  if (HOLD) {
-    load_sub<VEC>(trow, j * SUBW, min(V, j * SUBW + SUBW), lt0);
-    load_sub<VEC>(drow, j * SUBW, min(V, j * SUBW + SUBW), ld0);
-  }
-  // f(sp, e, x, target logit, draft logit) for every entry x < V of the piece, in order
-  auto entries = [&](auto&& f) {
-    if (HOLD) {
-      const int base = j * SUBW + tid * EPT;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if (base + e < V) f(0, e, base + e, lt0[e], ld0[e]);
-    } else {
-#pragma unroll 1
-      for (int sp = 0; sp < SUB; ++sp) {
-        const int x0 = (j * SUB + sp) * SUBW;
-        if (x0 >= V) break;
-        float ta[EPT], da[EPT];
-        load_sub<VEC>(trow, x0, min(V, x0 + SUBW), ta);
-        load_sub<VEC>(drow, x0, min(V, x0 + SUBW), da);
-        const int base = x0 + tid * EPT;
-#pragma unroll
-        for (int e = 0; e < EPT; ++e)
-          if (base + e < V) f(sp, e, base + e, ta[e], da[e]);
-      }
-    }
-  };
-  // n's children in index order (every piece of the row lists them the same way)
-  if (wave == 0) {
-    const int k0 = lane, k1 = lane + 64;
-    const bool c0 = k0 > n && k0 < T && a.parent[rb + k0] == n;
-    const bool c1 = k1 > n && k1 < T && a.parent[rb + k1] == n;
-    const uint64_t b0 = __ballot(c0), b1 = __ballot(c1);
-    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    if (c0) sh.sib[__builtin_popcountll(b0 & below)] = k0;
-    if (c1) sh.sib[__builtin_popcountll(b0) + __builtin_popcountll(b1 & below)] = k1;
-    if (lane == 0) {
-      sh.nsib = __builtin_popcountll(b0) + __builtin_popcountll(b1);
-      sh.gave_up = 0;
-    }
-  }
-
-  // ---- the piece's statistics: maxima and sums of exp((l - max) / tau), target and draft.  A one-part piece
-  // takes its thread's maxima first and keeps the exponentials relative to them, from which p and q follow by
-  // one factor each; a streamed piece re-references its sums when a maximum grows.
-  float mt = -INFINITY, md = -INFINITY;
-  double st = 0.0, sd = 0.0;
-  double et[EPT], ed[EPT];   // (one-part pieces)
-  if (HOLD) {
-    const int base = j * SUBW + tid * EPT;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if (base + e < V) {
-        mt = fmaxf(mt, lt0[e]);
-        md = fmaxf(md, ld0[e]);
-      }
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const bool in = base + e < V;
-      et[e] = in ? scaled_exp((double)lt0[e] - (double)mt, a.inv_tau, sh.tab) : 0.0;
-      ed[e] = in ? scaled_exp((double)ld0[e] - (double)md, a.inv_tau, sh.tab) : 0.0;
-      st += et[e];
-      sd += ed[e];
-    }
-  } else {
-    entries([&](int, int, int, float t, float d) {
-      if (t > mt) {
-        if (st != 0.0) st *= scaled_exp((double)mt - (double)t, a.inv_tau, sh.tab);
-        mt = t;
-      }
-      if (d > md) {
-        if (sd != 0.0) sd *= scaled_exp((double)md - (double)d, a.inv_tau, sh.tab);
-        md = d;
-      }
-      st += scaled_exp((double)t - (double)mt, a.inv_tau, sh.tab);
-      sd += scaled_exp((double)d - (double)md, a.inv_tau, sh.tab);
-    });
-  }
-  const float mt_own = mt, md_own = md;
-  const float bt = block_max(mt, sh), bd = block_max(md, sh);
-  if (st != 0.0) st *= scaled_exp((double)mt - (double)bt, a.inv_tau, sh.tab);
-  if (sd != 0.0) sd *= scaled_exp((double)md - (double)bd, a.inv_tau, sh.tab);
-  st = block_sum(st, sh);
-  sd = block_sum(sd, sh);
-  if (tid == 0) {
-    double* ps = a.piece_stat + (row * a.chunks + j) * 4;
-    store_d(ps + 0, bt);
-    store_d(ps + 1, st);
-    store_d(ps + 2, bd);
-    store_d(ps + 3, sd);
-    wait_vector_memory();
-    uint32_t* w = stats_word(a, b, n);
-    __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // every piece of the row
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    while (__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)a.chunks) {
-      if (__builtin_amdgcn_s_memrealtime() - t0 > a.wait_ticks) {
-        raise_device_error(a.err, kErrWaitTimeout);
-        sh.gave_up = 1;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  }
-  __syncthreads();
-  const RowStat rs = merge_stats(a, row, sh);
-  auto prob_p = [&](float t) { return scaled_exp((double)t - rs.mt, a.inv_tau, sh.tab) * rs.inv_st; };
-  auto prob_q = [&](float d) { return scaled_exp((double)d - rs.md, a.inv_tau, sh.tab) * rs.inv_sd; };
-  double pc[EPT], qc[EPT];   // (one-part pieces: the kept exponentials times one factor each)
-  if (HOLD) {
-    const double ft = mt_own == -INFINITY ? 0.0 : scaled_exp((double)mt_own - rs.mt, a.inv_tau, sh.tab) * rs.inv_st;
-    const double fd = md_own == -INFINITY ? 0.0 : scaled_exp((double)md_own - rs.md, a.inv_tau, sh.tab) * rs.inv_sd;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      pc[e] = et[e] * ft;
-      qc[e] = ed[e] * fd;
-    }
-  }
-
-  // ---- n's children in index order.  Child c (token x) is tested against the state (C, D) its earlier
-  // siblings left; its residual mass sum max(p - (C + D) q, 0) is summed over the row's pieces in its 64-bit
-  // accumulator (fixed point, so the sum does not depend on the order of arrival), and every piece waits for
-  // the whole sum before the next child.
+  pc.statistics();
   const int nsib = sh.nsib;
-  double C = 0.0, D = 1.0;
-  int src = -1;
-  for (int k = 0; k < nsib; ++k) {
-    const int c = sh.sib[k];
-    const int x = a.tokens[rb + c];
-    const double CC = C + D;
-    double z = 0.0, px = 0.0, qx = 0.0;
-    bool mine = false;
-    entries([&](int, int e, int xi, float t, float d) {
-      const double pe = HOLD ? pc[e] : prob_p(t), qe = HOLD ? qc[e] : prob_q(d);
-      z += fmax(pe - CC * qe, 0.0);
-      if (xi == x) {
-        px = pe;
-        qx = qe;
-        mine = true;
-      }
-    });
-    // c's decision, by the thread holding its token (a token outside the vocabulary is never kept)
-    if (mine) store_coherent(a.kept + rb + c, (int32_t)(((double)a.uniforms[rb + c] * qx) * D < fmax(px - C * qx, 0.0)));
-    if ((x < 0 || x >= V) && j == 0 && tid == 0) store_coherent(a.kept + rb + c, 0);
-    z = block_sum(z, sh);
-    if (tid == 0) {
-      // this piece's part of c's residual mass (read by the row's draw if c is the last child to move the
-      // state); the last child's arrival waits for every such store of the piece first
-      store_d(a.mass + (rb + c) * a.chunks + j, z);
-      if (k == nsib - 1) wait_vector_memory();
-      // A piece's mass is at most 1 (up to rounding); after a wait gave up it is meaningless and counts as 0,
-      // so that it can never carry into the arrival bits: the count, and with it the walk, still completes.
-      const double zc = sh.gave_up ? 0.0 : fmin(fmax(z, 0.0), 2.0);
-      const uint64_t fix = (uint64_t)rint(zc * kFixScale);
-      uint64_t* w = acc_word(a, b, c);
-      __hip_atomic_fetch_add(w, (1ull << kArrivalShift) + fix, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const uint64_t full = (uint64_t)a.chunks << kArrivalShift;
-      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      uint64_t v;
-      while (((v = load_u64(w)) & ~kMassMask) != full) {
-        if (__builtin_amdgcn_s_memrealtime() - t0 > a.wait_ticks) {
-          raise_device_error(a.err, kErrWaitTimeout);
-          sh.gave_up = 1;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      sh.st_c = (double)(v & kMassMask) * kFixUnit;   // c's whole residual mass
-    }
-    __syncthreads();
-    const double Zc = sh.st_c;
-    if (Zc > 0.0) {
-      C = CC;
-      D = Zc;
-      src = c;
-    }
-  }
-
-  // ---- the token emitted if the walk ends at n (every child rejected, or a leaf): drawn from max(p - C q, 0)
-  // through the inverse CDF with u0; the piece masses are those of child src's residual (every piece stored
-  // its part before its last arrival, which this piece has seen), or the target's own
-  if (src >= 0) {
-    const double* m = a.mass + (rb + src) * a.chunks;
-    for (int k = tid; k < a.chunks; k += NT) sh.pm[k] = load_d(m + k);
-  } else {
-    const double* ps = a.piece_stat + row * a.chunks * 4;
-    for (int k = tid; k < a.chunks; k += NT)
-      sh.pm[k] = load_d(ps + 4 * k + 1) * scaled_exp(load_d(ps + 4 * k + 0) - rs.mt, a.inv_tau, sh.tab) * rs.inv_st;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double total = 0.0;
-    for (int k = 0; k < a.chunks; ++k) total += sh.pm[k];
-    const double thr = (double)a.uniforms[rb] * total;
-    double cum = 0.0, before = 0.0, pos_before = 0.0;
-    int piece = -1, pos_piece = 0;
-    for (int k = 0; k < a.chunks; ++k) {
-      const double mk = sh.pm[k];
-      if (mk > 0.0) {
-        pos_piece = k;
-        pos_before = cum;
-      }
-      if (cum + mk > thr) {
-        piece = k;
-        before = cum;
-        break;
-      }
-      cum += mk;
-    }
-    if (piece < 0) {   // no crossing (an all-zero residual): the last piece of positive mass
-      piece = pos_piece;
-      before = pos_before;
-    }
-    sh.fin_piece = piece;
-    sh.fin_before = before;
-    sh.fin_thr = thr;
-  }
-  __syncthreads();
-  if (sh.fin_piece == j) {   // (one piece of the row draws)
-    const double thr = sh.fin_thr;
-    double before = sh.fin_before;
-    int pick = INT_MAX, last_pos = -1;
-    // part by part (a one-part piece has one): the block's prefix of r = max(p - C q, 0) in entry order
-#pragma unroll 1
-    for (int sp = 0; sp < SUB && pick == INT_MAX; ++sp) {
-      const int x0 = (j * SUB + sp) * SUBW;
-      if (x0 >= V) break;
-      const int base = x0 + tid * EPT;
-      float ta[EPT], da[EPT];
-      if (HOLD) {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          ta[e] = lt0[e];
-          da[e] = ld0[e];
-        }
-      } else {
-        load_sub<VEC>(trow, x0, min(V, x0 + SUBW), ta);
-        load_sub<VEC>(drow, x0, min(V, x0 + SUBW), da);
-      }
-      double r[EPT], mine_sum = 0.0;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        r[e] = 0.0;
-        if (base + e < V) {
-          const double pe = HOLD ? pc[e] : prob_p(ta[e]);
-          const double qe = C == 0.0 ? 0.0 : (HOLD ? qc[e] : prob_q(da[e]));
-          r[e] = fmax(pe - C * qe, 0.0);
-        }
-        mine_sum += r[e];
-      }
-      double total;
-      double cum = before + block_exclusive_scan(mine_sum, total, sh);
-      int pk = INT_MAX, lp = -1;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        cum += r[e];
-        if (pk == INT_MAX && cum > thr) pk = base + e;
-        if (r[e] > 0.0) lp = base + e;
-      }
-      pick = block_int<false>(pk, sh);
-      last_pos = max(last_pos, block_int<true>(lp, sh));
-      before += total;
-    }
-    // (rounding between the piece masses and this prefix can leave the crossing just outside the piece: then
-    // the piece's last entry of positive mass)
-    if (pick == INT_MAX) pick = last_pos >= 0 ? last_pos : min(V - 1, j * SUB * SUBW);
-    if (tid == 0) store_coherent(a.final_token + row, pick);
-    wait_vector_memory();
-  }
-  // Every piece counts itself out on the row's statistics word (which already holds one arrival per piece),
-  // once its decisions and token are stored; the row's last piece counts the row as done, and the sequence's
-  // last row runs the walk.  (So each row is counted once even where a wait gave up and the pieces disagree on
-  // which one draws.)
+  for (int k = 0; k < nsib && !sh.gave_up; ++k) pc.test_child(sh.sib[k], k == nsib - 1);
+  const int pick = pc.draw();
+  if (pick >= 0 && tid == 0) store_coherent(a.final_token + row, pick);
+  // Every piece counts itself out once its decisions and token are stored; the row's last piece counts the row
+  // as done, and the sequence's last row runs the walk.
   wait_vector_memory();
   __syncthreads();
+  if (tid == 0)
+    sh.flag = pc.leave() && __hip_atomic_fetch_add(a.seq_ctr + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                                (uint32_t)(T - 1);
+  __syncthreads();
+  if (sh.flag) walk_decisions(a, b, sh);
+}
+
+// --------------------------------------------------------------------------------------------- walk form
+// Workgroup (b, j): piece j of every row that sequence b's walk visits, from the root down.
+template <bool VEC, bool HOLD, int NT, int E>
+__global__ __launch_bounds__(NT) void tree_accept_sampled_walk_kernel(SampledArgs a) {
+  __shared__ Shared sh;
+  const int tid = threadIdx.x, T = a.T;
+  const int b = (int)(blockIdx.x / (unsigned)a.chunks), j = (int)(blockIdx.x % (unsigned)a.chunks);
+  const size_t rb = (size_t)b * T;
+  Piece<VEC, true, HOLD, NT, E> pc(a, sh, b, j, a.seq_ctr + b, b);
+  pc.enter();
+  pc.load(0);
+  if (tid < 256) sh.tab[tid] = exp2((double)tid * (1.0 / 256.0));
+  if (tid < T) sh.par[tid] = a.parent[rb + tid];
   if (tid == 0) {
-    int walker = 0;
-    if (__hip_atomic_fetch_add(stats_word(a, b, n), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-        (uint32_t)(2 * a.chunks - 1))
-      walker = __hip_atomic_fetch_add(a.seq_ctr + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(T - 1);
-    sh.flag = walker;
+    sh.gave_up = sh.keep_here = 0;
+    sh.path[0] = 0;
   }
   __syncthreads();
-  if (sh.flag) walk(a, b, sh);
-}
-
-template <bool VEC, int SUB>
-__global__ __launch_bounds__(NT) void tree_accept_sampled_kernel(SampledArgs a) {
-  __shared__ Shared sh;
-  sh.tab[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 256.0));
-  __syncthreads();
-  const long long t = blockIdx.x;
-  const int j = (int)(t % a.chunks);
-  const long long r = t / a.chunks;
-  row_piece<VEC, SUB, kSampledPerThreadRow>(a, (int)(r / a.T), (int)(r % a.T), j, sh);
-}
-
-template <bool VEC, int SUB>
-__global__ __launch_bounds__(NT) void tree_accept_sampled_split_kernel(SampledArgs a) {
-  __shared__ Shared sh;
-  sh.tab[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 256.0));
-  __syncthreads();
-  const long long t = blockIdx.x;
-  const long long stats = (long long)a.B * a.T * a.chunks;
-  if (t < stats) {
-    const int j = (int)(t % a.chunks);
-    const long long r = t / a.chunks;
-    stats_piece<VEC, SUB>(a, (int)(r / a.T), (int)(r % a.T), j, sh);
-  } else {
-    const long long u = t - stats;
-    const long long per_child = (long long)a.B * a.chunks;
-    const int c = 1 + (int)(u / per_child);
-    const long long v = u % per_child;
-    pass_piece<VEC, SUB>(a, (int)(v / a.chunks), c, (int)(v % a.chunks), sh);
+  int depth = 0;
+  for (int node = 0;;) {
+    if (tid < 64) list_children(node, T, sh.par, sh);
+    pc.statistics();
+    const int nsib = sh.nsib;
+    int next = -1;
+    for (int k = 0; k < nsib && next < 0 && !sh.gave_up; ++k) {
+      const int c = sh.sib[k];
+      if (pc.test_child(c, k == nsib - 1)) next = c;
+    }
+    if (next < 0 || sh.gave_up) break;
+    node = next;
+    ++depth;
+    if (tid == 0) sh.path[depth] = node;
+    pc.load(node);
+    __syncthreads();   // every thread has read this node's children and whether a wait gave up
   }
+  const int pick = pc.draw();
+  if (pick >= 0 && tid == 0) a.next_token[b] = pick;
+  if (j == 0) {
+    if (tid < T) a.accept_path[rb + tid] = tid <= depth ? sh.path[tid] : -1;
+    if (tid == 0) a.accept_len[b] = depth;
+  }
+  wait_vector_memory();
+  __syncthreads();
+  if (tid == 0 && pc.leave()) reset_counter(a.seq_ctr + b);
 }
 
 }  // namespace
 
 hipError_t launch_tree_accept_sampled(const SampledArgs& a, hipStream_t stream) {
-  static_assert(NT == 256, "the exp table is filled one entry per thread");
-  // one-part pieces: a workgroup per row piece; four-part pieces (problems of many pieces): the split form
-  const bool large = a.sub_pieces == kSampledSubLarge;
-  const long long grid = large ? (long long)a.B * (2 * a.T - 1) * a.chunks : (long long)a.B * a.T * a.chunks;
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), 0, stream, a); };
-  if (a.vec4) {
-    if (large) go(tree_accept_sampled_split_kernel<true, kSampledSubLarge>);
-    else go(tree_accept_sampled_kernel<true, 1>);
-  } else {
-    if (large) go(tree_accept_sampled_split_kernel<false, kSampledSubLarge>);
-    else go(tree_accept_sampled_kernel<false, 1>);
+  if (a.chunks > kSampledMaxPieces) return hipErrorInvalidValue;
+  const long long grid = (long long)a.B * (a.walk ? 1 : a.T) * a.chunks;
+  auto go = [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, stream, a);
+    return hipGetLastError();
+  };
+  if (!a.walk)
+    return a.vec4 ? go(tree_accept_sampled_rows_kernel<true, 512, 8>, 512)
+                  : go(tree_accept_sampled_rows_kernel<false, 512, 8>, 512);
+#define DREAMS_WALK(HOLD, NT, E)                                                        \
+  return a.vec4 ? go(tree_accept_sampled_walk_kernel<true, HOLD, NT, E>, NT)            \
+                : go(tree_accept_sampled_walk_kernel<false, HOLD, NT, E>, NT)
+  if (a.sub_pieces > 1) DREAMS_WALK(false, 1024, 8);
+  switch (a.part) {
+    case 2048: DREAMS_WALK(true, 512, 4);
+    case 4096: DREAMS_WALK(true, 1024, 4);
+    case 8192: DREAMS_WALK(true, 1024, 8);
+    case 10240: DREAMS_WALK(true, 1024, 10);
   }
-  return hipGetLastError();
+#undef DREAMS_WALK
+  return hipErrorInvalidValue;
 }
 
 }  // namespace dreams

@@ -204,3 +204,28 @@ def test_out_of_range_tokens_are_rejected(dev):
     ra, rp, rn = oracle.tree_accept_sampled(tl_ref, dl, tok_ref, par, uni, 1.0)
     assert np.array_equal(ga, ra) and np.array_equal(gp, rp) and np.array_equal(gn, rn)
     assert np.all(gn != V - 1)
+
+
+@pytest.mark.parametrize("B,T,V", [
+    (4, 40, 30000),      # the walk form's parts: 2048 entries
+    (16, 12, 30001),     # ... with scalar loads
+    (20, 10, 40000),     # 4096
+    (36, 8, 40000),      # 8192
+    (40, 6, 50000),      # 10240
+    (40, 5, 110000),     # 10240, more workgroups than compute units
+    (130, 9, 3000),      # a row in one workgroup
+    (16, 40, 8192),
+    (1, 6, 700000),      # several parts per piece, streamed
+    (2, 5, 700001),
+])
+def test_walk_form(dev, B, T, V):
+    """Enough row pieces (or a vocabulary too long for the row form) that each sequence is walked by its own
+    workgroups, in every size of part; the workspace's counters return to zero."""
+    assert B * T * ((V + 4095) // 4096) > 1024 or V > 64 * 4096
+    rng = np.random.default_rng(V + B)
+    tl, dl, tok, par, uni = random_case(rng, B, T, V, min(T - 1, 6), 4, noise=0.7)
+    ws = torch.zeros(dreams.tree_accept_sampled_workspace_size(B, T, V), dtype=torch.uint8, device=dev)
+    ws[65536:] = 0xA5                    # (only the counter region has to be zero)
+    for _ in range(2):
+        run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "walk form %s" % ((B, T, V),), workspace=ws)
+    assert not ws[:65536].any()
