@@ -179,10 +179,10 @@ struct AcceptPlan {
   size_t val_off, idx_off, bytes;
 };
 
-// Pieces of a row: 8192 logits (8 16-byte loads per thread) while the batch has fewer rows than about two
-// workgroups per compute unit, so that the logits spread over the whole chip; otherwise up to 32768 logits
-// (32 loads per thread) per piece, so that most rows are one piece and need no second merge level.
-constexpr int kAcceptSmallPiece = 8192, kAcceptLargePiece = 32768, kAcceptTargetWgs = 512;
+// Pieces of a row: 8192 logits while the batch has fewer rows than about two workgroups per compute unit, so that
+// the logits spread over the whole chip; otherwise whole rows (16 x 128 x 152064 in pieces of 16384: 211 us, 32768:
+// 204, 65536: 197, whole: 193), which need no second merge level either.
+constexpr int kAcceptSmallPiece = 8192, kAcceptLargePiece = 1 << 18, kAcceptTargetWgs = 512;
 constexpr int kAcceptGroups = 8;   // group counters per sequence (see tree_accept.hip)
 
 dreams_status_t plan_accept(int32_t B, int32_t T, int32_t V, AcceptPlan* p) {
@@ -226,7 +226,14 @@ dreams_status_t plan_accept(int32_t B, int32_t T, int32_t V, AcceptPlan* p) {
     p->group_base = 0;
     p->group_stride = 1;
   }
-  const size_t parts = (size_t)rows * chunks;
+  // (room for pieces of 32768 logits at least, so that a workspace sized for a large batch serves smaller ones,
+  // whose rows are cut into more pieces)
+  long long room = ((long long)V + 32767) / 32768;
+  if (room > kAcceptMaxChunks) room = kAcceptMaxChunks;
+  long long unit = (V + room - 1) / room;
+  unit = (unit + 3) / 4 * 4;
+  room = (V + unit - 1) / unit;
+  const size_t parts = (size_t)rows * (chunks > room ? chunks : room);
   p->val_off = kCounterBytes;
   p->idx_off = p->val_off + align_up(parts * sizeof(float), 256);
   p->bytes = p->idx_off + align_up(parts * sizeof(int32_t), 256);
@@ -477,7 +484,6 @@ dreams_status_t dreams_tree_accept(int32_t batch, int32_t num_nodes, int32_t voc
   a.group_stride = p.group_stride;
   a.chunks = p.chunks;
   a.chunk = p.chunk;
-  a.vec4 = (vocab % 4 == 0) && aligned(target_logits, 16);
   hipError_t e = launch_tree_accept(a, stream);
   if (e != hipSuccess) return hip_fail(e, "tree accept launch");
   return ok();

@@ -186,8 +186,7 @@ struct AcceptArgs {
   int group_base;         // word index of the first group counter
   int group_stride;       // words between consecutive group counters (32: a 128-byte line each)
   int chunks;             // vocabulary pieces per row
-  int chunk;              // elements per piece (multiple of 4 when vectorised)
-  int vec4;               // logits rows are 16-byte aligned and V % 4 == 0
+  int chunk;              // elements per piece
 };
 
 hipError_t launch_tree_accept(const AcceptArgs& a, hipStream_t stream);

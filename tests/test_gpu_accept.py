@@ -112,3 +112,24 @@ def test_workspace_reuse_and_repeat(dev):
     for o in outs[1:]:
         for x, y in zip(o, outs[0]):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("B,T,V", [(6, 100, 1), (6, 100, 3), (6, 100, 5), (6, 100, 4095), (6, 100, 4097), (6, 100, 8193),
+                                   (2, 7, 16383), (2, 7, 8191), (5, 128, 40001)])
+def test_unaligned_rows(dev, B, T, V):
+    """Odd vocabularies: rows begin at every word of a 16-byte vector; with ties planted at both ends of the row,
+    at the ends of its vectors, and in the first and last piece, the smallest index wins."""
+    rng = np.random.default_rng(V)
+    parent = np.stack([W.random_tree(rng, T, min(T - 1, 6), 6) for _ in range(B)])
+    logits = rng.standard_normal((B, T, V)).astype(np.float32)
+    edges = [x for x in (0, 1, 2, 3, 4, 5, V // 2, V - 6, V - 5, V - 4, V - 3, V - 2, V - 1) if 0 <= x < V]
+    for b in range(B):
+        for i in range(T):
+            for x in rng.choice(edges, size=2):
+                logits[b, i, x] = 9.0
+    tokens = rng.integers(0, V, (B, T)).astype(np.int32)
+    for shift in range(4):               # ... and the tensor itself at every word
+        big = torch.zeros(B * T * V + 4, dtype=torch.float32, device=dev)
+        big[shift:shift + B * T * V] = to_dev(logits.reshape(-1), dev)
+        run_and_compare(dev, logits, tokens, parent, "V=%d shift %d" % (V, shift),
+                        logits_dev=big[shift:shift + B * T * V].view(B, T, V))
