@@ -105,6 +105,7 @@ struct AttnArgs {
   int max_keys;           // host-side bound on L_b + T over the batch (plans the pieces of the key axis)
   int piece_by_len;       // 1: each sequence's pieces are cut from its own L_b + T (read before the first copies)
   float scale_log2;       // scale * log2(e)
+  int cus;                // compute units of the device (fp32: rows per workgroup)
 };
 
 // Query rows per workgroup the bf16 kernel uses for G*T rows per KV head.

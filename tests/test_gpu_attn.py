@@ -135,6 +135,35 @@ def test_fp32_path(dev, case):
     assert err <= ATTN_TOL_F32 and lerr <= 1e-4
 
 
+F32_ROW_CASES = [  # as above; batch 2, so 2 Hq T rows: 1, 2 and 4 rows per workgroup
+    (64, 3, 3, 29, 5, 3, 257, False, False),      # 174 rows; one key past four groups of keys of every wave
+    (128, 5, 1, 43, 6, 4, 129, True, True),       # 430 rows, 215 per KV head: a last workgroup of one row
+    (64, 6, 2, 101, 8, 6, 40, False, False),      # 1212 rows, 303 per KV head: a last workgroup of three rows
+    (128, 6, 3, 128, 8, 6, 63, True, False),      # 1536 rows, four groups of tree keys per wave
+]
+
+
+@pytest.mark.parametrize("case", F32_ROW_CASES, ids=lambda c: "D%d_Hq%d_Hkv%d_T%d_L%d" % (c[0], c[1], c[2], c[3], c[6]))
+def test_fp32_rows_per_workgroup(dev, case):
+    test_fp32_path(dev, case)
+
+
+def test_fp32_hidden_values_do_not_reach_rows(dev):
+    # NaN and infinities in slots that a row does not see (tree slots off its path, slots past the end) leave it alone
+    wl = small_wl(head_dim=64, num_nodes=16, kv_len=70, dtype="f32")
+    batch = W.make_batch(wl, with_logits=False)
+    q, k, v, kv, par = layer_tensors(batch, 0, dev)
+    kv[:] = 60
+    out, lse = dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=70)
+    k2, v2 = k.clone(), v.clone()
+    for t, bad in ((k2, float("nan")), (v2, float("inf"))):
+        t[:, :, 60 + 16:] = bad
+        t[:, :, 60 + 15] = bad      # the last node: no other row's ancestor
+    out2, lse2 = dreams.tree_verify_attn(q, k2, v2, kv, par, max_kv_len=70)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :, :15], out2[:, :, :15]) and torch.equal(lse[:, :, :15], lse2[:, :, :15])
+
+
 CASES = [  # (D, Hq, Hkv, T, depth, branch, L, splits)
     (128, 4, 2, 16, 4, 3, 300, 0),
     (128, 4, 2, 16, 4, 3, 300, 1),
