@@ -122,3 +122,17 @@ def test_prefill_repeatable_and_counters_clear(dev):
         for a, b in zip(outs[0], o):
             assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
     assert not ws[:65536 - 128].cpu().numpy().any()
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 3), (2, 3, 5), (1, 4, 1024), (1, 8, 1025), (2, 16, 1027), (1, 32, 2051)],
+                         ids=lambda s: "%dx%dx%d" % s)
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_prefill_entropy_mean_sizes(dev, shape, offset):
+    # whole vectors, remainders and unaligned starts: the fp64 mean to one fp32 rounding
+    n = int(np.prod(shape))
+    buf = torch.rand(n + offset + 4, device=dev, generator=torch.Generator(device=dev).manual_seed(n)) * 8
+    ent = buf[offset:offset + n].view(shape)
+    ae = dreams.prefill_attn_entropy_mean(ent, torch.full((shape[0],), shape[2], dtype=torch.int32, device=dev))
+    torch.cuda.synchronize()
+    ref = float(ent.double().sum() / n)
+    assert abs(float(ae) - ref) <= 2.0 ** -24 * ref * 1.01
