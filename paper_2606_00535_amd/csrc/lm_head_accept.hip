@@ -199,18 +199,36 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   const __bf16* xsrc = a.hidden + (size_t)min(m0 + xr, a.M - 1) * H + 8 * xc;
   const int xw = xr * 128 + ((xc ^ (xr & 7)) << 4);
 
+  // The hidden axis in quarters: a workgroup starts at quarter nt % 4 and wraps round, so that the workgroups,
+  // which keep in step, do not all read the same 1 KB of their 8 KB rows at a time (which the memory channels
+  // serve unevenly: 54.8 us with all of them from quarter 0, 44.3 us so, at 60 rows x 32000 x 4096, 5.9 TB/s).  Each quarter has its own sums,
+  // added in one order wherever the workgroup started, so equal weight rows of different tiles still tie.
+  const int quarter = nstages / 4, start = (nt & 3) * quarter;
   bf16x8 hv[LM_DW];
   auto issue = [&](int slot, int s) {
-    const int k = min(s, nstages - 1) * LM_SK;   // (stages past the end repeat the last one, unused)
+    int ks = min(s, nstages - 1) + start;   // (stages past the end repeat the last one, unused)
+    if (ks >= nstages) ks -= nstages;
+    const int k = ks * LM_SK;
     const uint32_t dst = wring_lds + slot * LM_WSLOT;
     copy16_to_lds<true>(dst, wsrc0 + k);
     copy16_to_lds<true>(dst + 1024, wsrc1 + k);
     load16_async(hv[slot], xsrc + k);
   };
-  f32x4 acc[4];
+  f32x4 acc[4], done[3][4];   // the current quarter's sums; those of the quarters before it, the latest first
 #pragma unroll
-  for (int r = 0; r < 4; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int r = 0; r < 4; ++r) acc[r] = done[0][r] = done[1][r] = done[2][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int boundary = quarter;   // the next quarter's first stage
   auto compute = [&](int slot, int s) {
+    if (s == boundary) {   // (the last products into acc were issued a barrier ago)
+      boundary += quarter;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        done[2][r] = done[1][r];
+        done[1][r] = done[0][r];
+        done[0][r] = acc[r];
+        acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
     const char* wst = wring + ((size_t)wave * LM_DW + slot) * LM_WSLOT;
     const char* xst = xs + (size_t)(s % LM_XBUF) * LM_XSTAGE;
 #pragma unroll
@@ -244,7 +262,18 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
       compute(j, s);
     }
   }
-  wait_vm<0>();   // copies issued past the last stage land before the workgroup's LDS is released
+  // copies issued past the last stage land before the workgroup's LDS is released, loads before their registers are
+  // used for anything else
+  asm volatile("s_waitcnt vmcnt(0)"
+               : "+v"(hv[0]), "+v"(hv[1]), "+v"(hv[2]), "+v"(hv[3]), "+v"(hv[4]), "+v"(hv[5]), "+v"(hv[6]), "+v"(hv[7])
+               :
+               : "memory");
+  static_assert(LM_DW == 8, "every load register is tied to the wait");
+  // (q0 + q1) + (q2 + q3) of the quarters in the row's own order; the first one taken was quarter nt % 4
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    acc[r] = (nt & 1) ? (acc[r] + done[2][r]) + (done[1][r] + done[0][r])
+                      : (done[2][r] + done[1][r]) + (done[0][r] + acc[r]);
 
   // lane (col, quad) of wave w: rows 16 r + col, vocabulary entries n0 + 4 quad + e
 #pragma unroll

@@ -136,6 +136,26 @@ def test_ties_go_to_the_smallest_index(dev):
     np.testing.assert_array_equal(gam, ref_am)
 
 
+@pytest.mark.parametrize("H", [256, 1280, 2304])
+def test_equal_rows_of_different_tiles_tie(dev, H):
+    """One weight row repeated in tiles that start at different quarters of the hidden axis (of 1, 5 and 9 stages):
+    its logits are bit-identical, so every row that prefers it takes the first copy."""
+    rng = np.random.default_rng(H)
+    B, T, V = 1, 40, 900
+    hid, wt = draw(rng, B, T, H, V)
+    h32 = W.bf16_bits_to_f32(hid).reshape(-1, H)
+    wt[50::128] = bf16_bits(h32.sum(axis=0) * rng.uniform(0.2, 1.0, H))
+    parent = W.random_tree(rng, T, 4, 3)[None]
+    logits = expected_argmax(hid, wt)[1]
+    prefers = logits.argmax(axis=1) % 128 == 50
+    assert prefers.sum() >= T // 4
+    _, _, _, am = dreams.tree_accept_lm_head(to_bf16_dev(hid, dev), to_bf16_dev(wt, dev),
+                                             torch.zeros((B, T), dtype=torch.int32, device=dev),
+                                             torch.from_numpy(parent).to(dev), want_target_argmax=True)
+    torch.cuda.synchronize()
+    assert np.all(am.cpu().numpy().reshape(-1)[prefers] == 50)
+
+
 def test_large_batch_sampled_rows(dev):
     """The gqa_long shape (16 sequences of 128 nodes, hidden 3584, vocabulary 152064): the oracle checks 96
     sampled rows' argmax; every sequence's path must follow the greedy rule on the kernel's tokens."""
