@@ -6,15 +6,22 @@
 //     entropy[h,i] = -sum_{j <= i} A[h,i,j] log A[h,i,j],   A[h,i,j] = exp(scale * q_i . k_j - lse[h,i]).
 // No value product is needed, so this is half of a causal attention forward.
 //
-//   * prefill_stats_kernel: a workgroup of 8 waves owns 256 query rows of one query head; a wave owns 32 rows
+//   * prefill_stats_kernel: a workgroup of 8 waves owns 128 query rows of one query head; a wave owns 32 rows
 //     as two 16-row matrix-core B operands (its queries stay in registers).  The prompt's keys 0 .. the
-//     workgroup's last row stream through an LDS ring of 64-key stages (LDS-DMA copies, several stages ahead)
-//     that all eight waves read: S^T = K Q^T on v_mfma_f32_16x16x32_bf16 with the key rows as the A operand.
+//     workgroup's last row stream through an LDS ring of 64-key stages (LDS-DMA copies, several stages ahead);
+//     four waves take each stage's first 32 keys, four its second 32 (their states meet in LDS at the end):
+//     S^T = K Q^T on v_mfma_f32_16x16x32_bf16 with the key rows as the A operand.
 //     Each lane keeps, for each of its 2 rows, an online (reference, sum, entropy term) over the keys its
 //     quad sees, in log2 units; the reference only moves when a score passes it by more than 2^8 (the sums
 //     stay finite and the statistics do not depend on it), and the four quads are merged at the end.  Only
-//     16-key blocks that cross the diagonal or the prompt's end are masked.  Workgroups are ordered so that
-//     the row blocks with the most keys start first and share a compute unit with those with the fewest.
+//     32-key blocks that cross the diagonal or the prompt's end are masked, in a loop of their own (in one loop
+//     the two paths' states met in register copies).  Workgroups are ordered so that the row blocks with the
+//     most keys start first; a single round's second half takes them in the opposite order.
+//     What bounds it is the vector ALU (77 % of its issue slots: per score an fma, an exp2 at a quarter rate,
+//     an add and an fma, beside a quarter of a matrix instruction), as long as every compute unit holds two
+//     workgroups to the end: 256-row workgroups left the longest alone with two waves a SIMD.  3136 rows x 32
+//     heads x 128: 85 us as 256-row workgroups, 72 us as 128-row ones, 63 us with the masked blocks apart, the
+//     maxima as three-input chains and the reference test on unscaled products (kernel times).
 //   * prefill_entropy_mean_kernel: one workgroup, the fp64 mean of the prompt rows' entropies over every head
 //     and sequence (rows i >= n_b hold 0 and do not count).
 #include "kernels.h"
@@ -31,7 +38,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 8;
 constexpr int kRB = 2;                        // 16-row blocks per wave
 constexpr int kRowsPerWave = 16 * kRB;
-constexpr int kRowsPerWg = kRowsPerWave * kWaves;
+constexpr int kKeyGroups = 2;                 // halves of a stage, each taken by half of the waves
+constexpr int kRowsPerWg = kRowsPerWave * kWaves / kKeyGroups;
 constexpr int kKeys = 64;                     // keys per ring stage
 constexpr int kStages = 4;                    // ring stages
 constexpr float kLazyLog2 = 8.0f;             // slack of the reference before it moves
@@ -119,8 +127,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
   constexpr int CPW = STAGE / 1024 / kWaves;     // wave-wide 1 KB copies per wave per stage
   static_assert(CPW >= 1 && CPW * 1024 * kWaves == STAGE, "copy split");
   extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];   // kStages x STAGE
-  // Workgroup order: row blocks with the most keys first, one per compute unit; the workgroups beyond the
-  // first round (which share a compute unit with one of the first) take the blocks in the opposite order, so
+  // Workgroup order: row blocks with the most keys first; if they all fit two to a compute unit, those beyond the
+  // first of each (which share a compute unit with one of the first) take the blocks in the opposite order, so
   // that the longest block is paired with the shortest.
   const int nblk = (a.N + kRowsPerWg - 1) / kRowsPerWg, BH = a.B * a.Hq;
   const int n = blockIdx.x, W = gridDim.x;
@@ -135,7 +143,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
   nb = nb < 0 ? 0 : (nb > a.N ? a.N : nb);
 
   const int r0 = blk * kRowsPerWg;                  // the workgroup's first row
-  const int rw0 = r0 + wave * kRowsPerWave;         // the wave's first row
+  constexpr int kRowWaves = kWaves / kKeyGroups;
+  const int kgrp = wave / kRowWaves;                // the wave's half of every stage
+  const int rw0 = r0 + (wave % kRowWaves) * kRowsPerWave;   // the wave's first row
   const size_t qrow0 = ((size_t)b * a.Hq + h) * a.N;
   const unsigned char* kbase = (const unsigned char*)a.k + ((size_t)b * a.Hkv + g) * a.S_cap * L::ROW;
   const int kend = min(r0 + kRowsPerWg, nb);        // keys any live row of the workgroup can see
@@ -178,112 +188,166 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
   }
 
   float m[kRB], l[kRB], e[kRB];
+  float thr[kRB];   // the products past which the reference moves: (m + kLazyLog2) / c, kept up by the plain blocks
 #pragma unroll
   for (int rb = 0; rb < kRB; ++rb) {
-    m[rb] = -INFINITY;
+    m[rb] = thr[rb] = -INFINITY;
     l[rb] = 0.f;
     e[rb] = 0.f;
   }
   const int ka_row = (col & 3) * 4 + (col >> 2);   // A row m holds key kb*16 + (m%4)*4 + m/4
   const int wlast = min(rw0 + kRowsPerWave, nb) - 1;   // the wave's last live row (< rw0: none)
 
-  // a 16-key block: lane (col, quad) gets keys kk0 + 4 t + quad (t = 0..3) of rows rw0 + 16 rb + col
-  auto block = [&](const unsigned char* tile, int kb, int kk0) {
-    bf16x8 kf[DS];
+  // The wave's 32 keys of a stage (two 16-key blocks): lane (col, quad) gets keys kk0 + 16 kb + 4 t + quad
+  // (t = 0..3) of rows rw0 + 16 rb + col.
+  auto products = [&](f32x4 (&s)[kRB][2], const unsigned char* tile) {
+    bf16x8 kf[2][DS];
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) kf[ds] = *(const bf16x8*)(tile + L::off(kb * 16 + ka_row, ds * 4 + quad));
-    f32x4 s[kRB];
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) s[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int ds = 0; ds < DS; ++ds)
+        kf[kb][ds] = *(const bf16x8*)(tile + L::off((kgrp * 2 + kb) * 16 + ka_row, ds * 4 + quad));
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds)
 #pragma unroll
-      for (int rb = 0; rb < kRB; ++rb) s[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ds], qf[rb][ds], s[rb], 0, 0, 0);
-    const bool edge = kk0 + 15 > rw0 || kk0 + 16 > nb;   // (wave-uniform) a key past some row or the prompt
-    if (!edge) {
-      // every key visible: the reference moves (rarely) when a score passes it by more than 2^8, then each
-      // score costs one fma, one exp2, one add and one fma
-      float zmax[kRB];
-      bool grow = false;
-#pragma unroll
-      for (int rb = 0; rb < kRB; ++rb) {
-        zmax[rb] = c * vmax(vmax(s[rb][0], s[rb][1]), vmax(s[rb][2], s[rb][3]));
-        grow |= zmax[rb] > m[rb] + kLazyLog2;
-      }
-      if (__any(grow)) {
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int rb = 0; rb < kRB; ++rb)
-          if (zmax[rb] > m[rb] + kLazyLog2) rescale(m[rb], l[rb], e[rb], zmax[rb]);
-      }
+          s[rb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ds], qf[rb][ds],
+                                                              ds == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[rb][kb], 0, 0, 0);
+  };
+  // every key visible: the reference moves (rarely) when a score passes it by more than 2^8, then each score costs
+  // one fma, one exp2, one add and one fma
+  auto plain_block = [&](const f32x4 (&s)[kRB][2]) {
+    float smax[kRB];
+    bool grow = false;
 #pragma unroll
-      for (int rb = 0; rb < kRB; ++rb) {
+    for (int rb = 0; rb < kRB; ++rb) {
+      // (a chain, so that every step is one three-input maximum)
+      float x = vmax(vmax(s[rb][0][0], s[rb][0][1]), s[rb][0][2]);
+      x = vmax(vmax(x, s[rb][0][3]), s[rb][1][0]);
+      x = vmax(vmax(x, s[rb][1][1]), s[rb][1][2]);
+      smax[rb] = vmax(x, s[rb][1][3]);
+      grow |= smax[rb] > thr[rb];
+    }
+    if (__any(grow)) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float d = fmaf(s[rb][t], c, -m[rb]);
-          const float p = __builtin_amdgcn_exp2f(d);
-          l[rb] += p;
-          e[rb] = fmaf(p, d, e[rb]);
+      for (int rb = 0; rb < kRB; ++rb)
+        if (smax[rb] > thr[rb]) {
+          rescale(m[rb], l[rb], e[rb], c * smax[rb]);
+          thr[rb] = (m[rb] + kLazyLog2) / c;
         }
-      }
-      return;
     }
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb) {
-      float z[4];
+      float ps, es;   // (the block among itself first: fewer roundings at the sums' size)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const float d = fmaf(s[rb][kb][t], c, -m[rb]);
+          const float p = __builtin_amdgcn_exp2f(d);
+          ps = kb + t == 0 ? p : ps + p;
+          es = kb + t == 0 ? p * d : fmaf(p, d, es);
+        }
+      l[rb] += ps;
+      e[rb] += es;
+    }
+  };
+  // blocks that cross the diagonal or the prompt's end
+  auto edge_block = [&](const f32x4 (&s)[kRB][2], int kk0) {
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb) {
+      float z[2][4], zmax = -INFINITY;
       const int row = rw0 + rb * 16 + col;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int key = kk0 + 4 * t + quad;
-        z[t] = (key > row || key >= nb) ? -INFINITY : s[rb][t] * c;
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int key = kk0 + kb * 16 + 4 * t + quad;
+          z[kb][t] = (key > row || key >= nb) ? -INFINITY : s[rb][kb][t] * c;
+        }
+        zmax = vmax(zmax, vmax(vmax(z[kb][0], z[kb][1]), vmax(z[kb][2], z[kb][3])));
       }
-      const float zmax = vmax(vmax(z[0], z[1]), vmax(z[2], z[3]));
       if (zmax > m[rb] + kLazyLog2) rescale(m[rb], l[rb], e[rb], zmax);
       if (m[rb] != -INFINITY) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float d = fmaxf(z[t] - m[rb], -1.0e4f);   // (a masked key: p = 0 and a zero term)
-          const float p = __builtin_amdgcn_exp2f(d);
-          l[rb] += p;
-          e[rb] = fmaf(p, d, e[rb]);
-        }
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float d = fmaxf(z[kb][t] - m[rb], -1.0e4f);   // (a masked key: p = 0 and a zero term)
+            const float p = __builtin_amdgcn_exp2f(d);
+            l[rb] += p;
+            e[rb] = fmaf(p, d, e[rb]);
+          }
       }
     }
   };
 
-  for (int st = 0; st < nst; ++st) {
+  auto next_stage = [&](int st) {
     // this wave's copies of stage st have landed (the later stages it issued may still be in flight)
     wait_vm_steps<CPW, kStages - 2>(min(nst, max(st + kStages - 1, kStages - 1)) - st - 1);
     barrier_lds();   // stage st complete for every wave; every wave is past stage st - 1, whose slot is free
     if (st + kStages - 1 < nst) issue(st + kStages - 1);
-    const unsigned char* tile = ring + (st % kStages) * STAGE;
-#pragma unroll
-    for (int kb = 0; kb < kKeys / 16; ++kb) {
-      const int kk0 = st * kKeys + kb * 16;
-      if (kk0 > wlast) break;   // (wave-uniform) no live row of this wave sees these keys
-      block(tile, kb, kk0);
-    }
+  };
+  // The wave's plain stages come first, then those it masks, then those that no live row of it sees; every wave
+  // passes every stage's barrier, in whichever loop.
+  constexpr int KPG = kKeys / kKeyGroups;
+  const int first = kgrp * KPG;   // the wave's first key of a stage
+  const int lim = min(rw0, nb - 1) - (KPG - 1) - first;   // plain: st * kKeys <= lim
+  const int plain = min(nst, lim >= 0 ? lim / kKeys + 1 : 0);
+  int st = 0;
+  for (; st < plain; ++st) {
+    next_stage(st);
+    f32x4 s[kRB][2];
+    products(s, ring + (st % kStages) * STAGE);
+    plain_block(s);
+  }
+  for (; st < nst; ++st) {
+    next_stage(st);
+    const int kk0 = st * kKeys + first;
+    if (kk0 > wlast) continue;   // (wave-uniform)
+    f32x4 s[kRB][2];
+    products(s, ring + (st % kStages) * STAGE);
+    edge_block(s, kk0);
   }
 
   wait_vm<0>();   // (a workgroup with no live row has not waited for its first copies)
 
-  // merge the four quads' states of every row (fixed order: xor 16, then xor 32)
+  // merge the four quads' states of every row (fixed order: xor 16, then xor 32), then the key groups' through LDS
+  auto merge = [](float& m1, float& l1, float& e1, float m2, float l2, float e2) {
+    const float M = fmaxf(m1, m2);
+    if (M != -INFINITY) {
+      rescale(m1, l1, e1, M);
+      rescale(m2, l2, e2, M);
+    }
+    m1 = M;
+    l1 += l2;
+    e1 += e2;
+  };
+  barrier_lds();   // every wave is done with the ring
+  float* st_lds = (float*)ring;   // [3][kRowsPerWg]: the second key group's states
+  const int rl0 = (wave % kRowWaves) * kRowsPerWave;
 #pragma unroll
   for (int rb = 0; rb < kRB; ++rb) {
 #pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {
-      const float mo = __shfl_xor(m[rb], off), lo = __shfl_xor(l[rb], off), eo = __shfl_xor(e[rb], off);
-      const float M = fmaxf(m[rb], mo);
-      float m1 = m[rb], l1 = l[rb], e1 = e[rb], m2 = mo, l2 = lo, e2 = eo;
-      if (M != -INFINITY) {
-        rescale(m1, l1, e1, M);
-        rescale(m2, l2, e2, M);
-      }
-      m[rb] = M;
-      l[rb] = l1 + l2;
-      e[rb] = e1 + e2;
+    for (int off = 16; off <= 32; off <<= 1)
+      merge(m[rb], l[rb], e[rb], __shfl_xor(m[rb], off), __shfl_xor(l[rb], off), __shfl_xor(e[rb], off));
+    if (kgrp == 1 && quad == 0) {
+      const int rl = rl0 + rb * 16 + col;
+      st_lds[rl] = m[rb];
+      st_lds[kRowsPerWg + rl] = l[rb];
+      st_lds[2 * kRowsPerWg + rl] = e[rb];
     }
-    const int row = rw0 + rb * 16 + col;
-    if (quad == 0 && row < a.N) {
+  }
+  barrier_lds();
+  if (kgrp != 0 || quad != 0) return;
+#pragma unroll
+  for (int rb = 0; rb < kRB; ++rb) {
+    const int rl = rl0 + rb * 16 + col;
+    merge(m[rb], l[rb], e[rb], st_lds[rl], st_lds[kRowsPerWg + rl], st_lds[2 * kRowsPerWg + rl]);
+    const int row = r0 + rl;
+    if (row < a.N) {
       const bool live = row < nb && l[rb] > 0.f;
       if (a.lse) a.lse[qrow0 + row] = live ? (m[rb] + __log2f(l[rb])) * 0.69314718055994530942f : -INFINITY;
       if (a.entropy) a.entropy[qrow0 + row] = live ? 0.69314718055994530942f * (__log2f(l[rb]) - e[rb] / l[rb]) : 0.f;
