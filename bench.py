@@ -300,7 +300,7 @@ def measure_prefill(torch, dev, args, N=3136, n_img=2880, H=32, D=128):
         st["imp"] = torch.empty((1, n_img), dtype=torch.float32, device=dev)
         st["keep"] = torch.empty((1, n_img // 5), dtype=torch.int32, device=dev)
         sets.append(st)
-    ws = torch.zeros(dreams.visual_importance_workspace_size(1, H, n_img), dtype=torch.uint8, device=dev)
+    ws = torch.zeros(dreams.prefill_visual_importance_workspace_size(1, H, n_img), dtype=torch.uint8, device=dev)
     verbs = {
         "stats": lambda st: dreams.prefill_attn_stats(st["q"], st["k"], st["pl"], lse=st["lse"], entropy=st["ent"]),
         "entropy_mean": lambda st: dreams.prefill_attn_entropy_mean(st["ent"], st["pl"], ae=st["ae"]),

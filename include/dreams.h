@@ -299,10 +299,17 @@ dreams_status_t dreams_prefill_attn_entropy_mean(int32_t batch, int32_t num_q_he
  *   importance[b,j] = (1 / (Hq * n_b)) * sum_h sum_{i < n_b} A[b,h,i,vis_begin+j]
  * (a slot past row i gets nothing from it; a slot at or past n_b has importance 0; n_b = 0 gives 0).  lse: the
  * [B, Hq, num_rows] output of dreams_prefill_attn_stats on the same inputs.  Requires vis_begin >= 0,
- * vis_count >= 1, vis_begin + vis_count <= num_rows.  workspace: as for dreams_visual_importance (size from
- * dreams_visual_importance_workspace_size(batch, num_kv_heads, vis_count); its counter region zero, and left
+ * vis_count >= 1, vis_begin + vis_count <= num_rows.  workspace: as for dreams_visual_importance (at least
+ * dreams_visual_importance_workspace_size(batch, num_kv_heads, vis_count) bytes; its counter region zero, and left
  * zero).  importance: device [B, vis_count] float (out).  The heads are summed in head order (reproducible).
+ *
+ * With few KV heads or visual tokens the rows of a head are cut into pieces for more workgroups, each with partial
+ * sums of its own in the workspace: dreams_prefill_visual_importance_workspace_size bytes hold all of them.  A
+ * smaller workspace gets as many pieces as it holds (a slower call, sums of fewer pieces in the same order).
  */
+dreams_status_t dreams_prefill_visual_importance_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t vis_count,
+                                                                size_t* bytes);
+
 dreams_status_t dreams_prefill_visual_importance(const dreams_prefill_desc_t* desc, const void* q, const void* k_cache,
                                                  const int32_t* prompt_len, const float* lse, int32_t vis_begin,
                                                  int32_t vis_count, float* importance, void* workspace,

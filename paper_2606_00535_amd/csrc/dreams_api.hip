@@ -754,6 +754,14 @@ static_assert(kVisualMaxTokens == DREAMS_VISUAL_MAX_TOKENS, "top-r capacity");
 size_t visual_workspace_bytes(int batch, int num_kv_heads, int vis_count) {
   return kCounterBytes + (size_t)batch * num_kv_heads * vis_count * sizeof(float);
 }
+// Pieces that a prompt's rows are cut into (a workgroup each per sequence, KV head and 256 tokens): as many as make
+// about three workgroups per compute unit, at most 16.  A call whose workspace has room for fewer gets those.
+constexpr int kVisualTargetWgs = 768, kVisualMaxPieces = 16, kVisualPieceStages = 4;
+int visual_pieces(int batch, int num_kv_heads, int vis_count) {
+  const long long wgs = (long long)batch * num_kv_heads * ((vis_count + 255) / 256);
+  const long long n = wgs > 0 ? (kVisualTargetWgs + wgs - 1) / wgs : 1;
+  return (int)(n < kVisualMaxPieces ? n : kVisualMaxPieces);
+}
 int visual_counter_stride(int batch, int vis_count) {   // 0: the counters do not fit
   const long long n = (long long)batch * ((vis_count + 255) / 256);
   int stride = kCounterStride;
@@ -884,6 +892,14 @@ dreams_status_t dreams_prefill_attn_entropy_mean(int32_t batch, int32_t num_q_he
   return ok();
 }
 
+dreams_status_t dreams_prefill_visual_importance_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t vis_count,
+                                                                size_t* bytes) {
+  dreams_status_t st = dreams_visual_importance_workspace_size(batch, num_kv_heads, vis_count, bytes);
+  if (st != DREAMS_OK) return st;
+  *bytes = kCounterBytes + (*bytes - kCounterBytes) * visual_pieces(batch, num_kv_heads, vis_count);
+  return ok();
+}
+
 dreams_status_t dreams_prefill_visual_importance(const dreams_prefill_desc_t* desc, const void* q, const void* k_cache,
                                                  const int32_t* prompt_len, const float* lse, int32_t vis_begin,
                                                  int32_t vis_count, float* importance, void* workspace,
@@ -920,6 +936,13 @@ dreams_status_t dreams_prefill_visual_importance(const dreams_prefill_desc_t* de
   a.counters = (uint32_t*)workspace;
   a.counter_stride = stride;
   a.partial = (float*)((char*)workspace + kCounterBytes);
+  a.pieces = visual_pieces(desc->batch, desc->num_kv_heads, vis_count);
+  // (no piece of the longest block under kVisualPieceStages stages of 64 rows)
+  const long long by_rows =
+      (long long)(desc->num_q_heads / desc->num_kv_heads) * ((desc->num_rows + 63) / 64) / kVisualPieceStages;
+  if (a.pieces > by_rows) a.pieces = by_rows > 1 ? (int)by_rows : 1;
+  const size_t held = (workspace_bytes - kCounterBytes) / (need - kCounterBytes);
+  if ((size_t)a.pieces > held) a.pieces = (int)held;
   a.importance = importance;
   a.B = desc->batch;
   a.Hq = desc->num_q_heads;

@@ -126,7 +126,8 @@ struct VisualArgs {
   // 0: the rows are a verification call's tree rows (every row sees the whole prefix); 1: the rows are a
   // prompt's own positions (T = the rows per head, row i sees slots 0..i, rows i >= kv_len[b] do not count)
   int prefill;
-  float* partial;         // [B, Hkv, vis_count] workspace
+  float* partial;         // [B, Hkv, pieces, vis_count] workspace
+  int pieces;             // prefill rows: runs that the rows of every block of tokens are cut into (else 1)
   uint32_t* counters;     // [B, ceil(vis_count / 256)] arrival counters, counter_stride words apart (zero)
   int counter_stride;
   float* importance;      // [B, vis_count]

@@ -178,7 +178,11 @@ __global__ __launch_bounds__(256) void visual_importance_kernel(VisualArgs a) {
 // read.  The key rows and query rows use the attention kernel's swizzled layout and operand order (A row m
 // holds block row (m%4)*4 + m/4), so every 16-byte operand read is bank-conflict free.  Workgroups are ordered
 // so that the blocks with the most rows (the first tokens) start first and share a compute unit with those
-// with the fewest.
+// with the fewest.  The rows of a block are cut into `pieces` runs of stages, a workgroup each, where the blocks of
+// all KV heads are too few or too unequal to keep two workgroups on every compute unit: LLaVA-7B's prompt (384
+// blocks of 1 to 49 stages) 95 us a call in one piece, 74 us in two; 28 query heads on 4 KV heads x 2000 rows (32
+// blocks) 321 us in one, 32 us in 16.  (Blocks of fewer tokens instead, the rows shared by the waves: 91 and 84 us,
+// as every block reads all of the rows.)
 namespace pf {
 constexpr int kWaves = 8, kTokPerWave = kImpKeys / kWaves, KB = kTokPerWave / 16;
 constexpr int kRows = 64, kStages = 4;
@@ -237,7 +241,9 @@ __global__ __launch_bounds__(64 * pf::kWaves, 2) void visual_importance_prefill_
   const int blocks = (a.vis_count + kImpKeys - 1) / kImpKeys, BG = a.B * a.Hkv;
   const int n = blockIdx.x, W = gridDim.x;
   const int rank = (n >= a.cus && W <= 2 * a.cus) ? W - 1 - (n - a.cus) : n;
-  const int blk = rank / BG, bg = rank - blk * BG;        // blocks of the first tokens (the most rows) first
+  const int P = a.pieces;
+  const int blk = rank / (BG * P);                        // blocks of the first tokens (the most rows) first
+  const int piece = (rank - blk * BG * P) / BG, bg = rank % BG;
   const int g = bg % a.Hkv, b = bg / a.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, quad = lane >> 4;
@@ -267,12 +273,27 @@ __global__ __launch_bounds__(64 * pf::kWaves, 2) void visual_importance_prefill_
   // rows that can see the block's tokens: i >= its first token's slot, in 64-row stages, head after head
   const int istart = min(L, max(0, a.vis_begin + blk * kImpKeys) & ~15);
   const int nsh = (L - istart + pf::kRows - 1) / pf::kRows;   // stages per head
-  const int nst = a.G * nsh;
+  const int t0 = (int)((long long)a.G * nsh * piece / P);   // this piece's stages [t0, t1)
+  const int t1 = (int)((long long)a.G * nsh * (piece + 1) / P);
   const size_t row0 = ((size_t)b * a.Hq + (size_t)g * a.G) * T;   // the KV head's first query row
   const unsigned char* qbase = (const unsigned char*)a.q + row0 * L_::ROW;
   const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(pf::lds_addr(ring));
+  // a stage's head and first row, advanced stage by stage
+  struct Place {
+    int hh, s0;
+  };
+  auto place = [&](int t) {
+    const int hh = t / max(nsh, 1);
+    return Place{hh, istart + (t - hh * nsh) * pf::kRows};
+  };
+  auto advance = [&](Place& p) {
+    p.s0 += pf::kRows;
+    if (p.s0 >= L) p = Place{p.hh + 1, istart};
+  };
+  Place ahead = place(t0), here = ahead;
   auto issue = [&](int t) {
-    const int hh = t / max(nsh, 1), s0 = istart + (t - hh * nsh) * pf::kRows;
+    const int hh = ahead.hh, s0 = ahead.s0;
+    advance(ahead);
     const uint32_t dst = __builtin_amdgcn_readfirstlane(ring_lds + (t % pf::kStages) * STAGE);
 #pragma unroll
     for (int jc = 0; jc < CPW; ++jc) {
@@ -292,14 +313,14 @@ __global__ __launch_bounds__(64 * pf::kWaves, 2) void visual_importance_prefill_
 #pragma unroll
   for (int kb = 0; kb < pf::KB; ++kb) acc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int first_slot = a.vis_begin + j0;   // the wave's first token's slot
-  const int pre = min(pf::kStages - 1, nst);
-  for (int t = 0; t < pre; ++t) issue(t);
-  for (int t = 0; t < nst; ++t) {
+  for (int t = t0; t < min(t0 + pf::kStages - 1, t1); ++t) issue(t);
+  for (int t = t0; t < t1; ++t) {
     // this wave's copies of stage t have landed (the later stages it issued may still be in flight)
-    pf::wait_vm_steps<OPS, pf::kStages - 2>(min(nst, t + pf::kStages - 1) - t - 1);
+    pf::wait_vm_steps<OPS, pf::kStages - 2>(min(t1, t + pf::kStages - 1) - t - 1);
     pf::barrier_lds();   // stage t complete for every wave; every wave is past stage t - 1, whose slot is free
-    if (t + pf::kStages - 1 < nst) issue(t + pf::kStages - 1);
-    const int hh = t / nsh, s0 = istart + (t - hh * nsh) * pf::kRows;
+    if (t + pf::kStages - 1 < t1) issue(t + pf::kStages - 1);
+    const int s0 = here.s0;
+    advance(here);
     if (s0 + pf::kRows - 1 < first_slot) continue;   // (wave-uniform) no row of the stage sees the wave's tokens
     const unsigned char* st = ring + (t % pf::kStages) * STAGE;
     const float* lse_s = (const float*)(st + QBYTES);
@@ -350,31 +371,36 @@ __global__ __launch_bounds__(64 * pf::kWaves, 2) void visual_importance_prefill_
       for (int e = 0; e < 4; ++e) {
         const int j = j0 + kb * 16 + e * 4 + quad;
         if (j < a.vis_count)
-          store_coherent(a.partial + ((size_t)b * a.Hkv + g) * a.vis_count + j, a.vis_begin + j < L ? acc[kb][e] : 0.f);
+          store_coherent(a.partial + (((size_t)b * a.Hkv + g) * P + piece) * a.vis_count + j,
+                         a.vis_begin + j < L ? acc[kb][e] : 0.f);
       }
   }
-  // The last of the sequence's KV heads to finish this block of tokens sums the heads' partials, in head
+  // The last of the sequence's KV heads' pieces to finish this block of tokens sums the partials, in head and piece
   // order (device-scope stores and loads; the counter is left at zero for the next call).
   __shared__ int last;
   wait_vector_memory();
   __syncthreads();
   if (tid == 0) {
     uint32_t* ctr = a.counters + ((size_t)b * blocks + blk) * a.counter_stride;
-    last = arrive_last(ctr, (uint32_t)a.Hkv);
+    last = arrive_last(ctr, (uint32_t)(a.Hkv * P));
     if (last) reset_counter(ctr);
   }
   __syncthreads();
   if (!last || tid >= kImpKeys) return;
   const int j = blk * kImpKeys + tid;
   if (j >= a.vis_count) return;
-  const float* pp = a.partial + (size_t)b * a.Hkv * a.vis_count + j;
+  const int parts = a.Hkv * P;
+  const float* pp = a.partial + (size_t)b * parts * a.vis_count + j;
   float sum = 0.f;
-  for (int g0 = 0; g0 < a.Hkv; g0 += 8) {
-    float x[8];
+  for (int g0 = 0; g0 < parts; g0 += 16) {
+    float x[16];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = g0 + k < a.Hkv ? load_coherent(pp + (size_t)(g0 + k) * a.vis_count) : 0.f;
+    for (int k = 0; k < 16; ++k) x[k] = g0 + k < parts ? load_coherent(pp + (size_t)(g0 + k) * a.vis_count) : 0.f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sum += x[k];
+    for (int w = 1; w < 16; w *= 2)   // (in pairs: as few roundings as the partials allow)
+#pragma unroll
+      for (int k = 0; k < 16; k += 2 * w) x[k] += x[k + w];
+    sum += x[0];
   }
   a.importance[(size_t)b * a.vis_count + j] = L > 0 ? sum / ((float)a.Hq * (float)L) : 0.f;
 }
@@ -539,8 +565,9 @@ hipError_t launch_visual_importance(const VisualArgs& a, hipStream_t stream) {
   const int blocks = (a.vis_count + kImpKeys - 1) / kImpKeys;
   const dim3 grid((unsigned)(a.B * a.Hkv * blocks));
   if (a.prefill) {
-    if (a.D == 128) return launch_importance_prefill<128>(a, grid, stream);
-    if (a.D == 64) return launch_importance_prefill<64>(a, grid, stream);
+    const dim3 all(grid.x * (unsigned)a.pieces);
+    if (a.D == 128) return launch_importance_prefill<128>(a, all, stream);
+    if (a.D == 64) return launch_importance_prefill<64>(a, all, stream);
     return hipErrorInvalidValue;
   }
   if (a.D == 128) hipLaunchKernelGGL(visual_importance_kernel<128>, grid, dim3(256), 0, stream, a);

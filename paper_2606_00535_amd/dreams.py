@@ -30,7 +30,7 @@ EXPORTS = (
     "dreams_tree_accept_sampled", "dreams_tree_accept_lm_head_workspace_size", "dreams_tree_accept_lm_head",
     "dreams_workspace_status", "dreams_tree_verify_attn_splits", "dreams_tree_verify_attn_noalloc",
     "dreams_set_wait_limit", "dreams_prefill_attn_stats", "dreams_prefill_attn_entropy_mean",
-    "dreams_prefill_visual_importance",
+    "dreams_prefill_visual_importance", "dreams_prefill_visual_importance_workspace_size",
 )
 
 
@@ -88,6 +88,7 @@ def lib():
                 L.dreams_attn_entropy_mean.argtypes = [ctypes.c_int64, P, P, P]
                 L.dreams_attn_entropy_select.argtypes = [I32, P, P, P]
                 L.dreams_visual_importance_workspace_size.argtypes = [I32, I32, I32, ctypes.POINTER(SZ)]
+                L.dreams_prefill_visual_importance_workspace_size.argtypes = [I32, I32, I32, ctypes.POINTER(SZ)]
                 L.dreams_visual_importance.argtypes = [ctypes.POINTER(AttnDesc), P, P, P, P, I32, I32, P, P, SZ, P]
                 L.dreams_visual_topk.argtypes = [I32, I32, I32, P, P, P]
                 L.dreams_tree_accept_sampled_workspace_size.argtypes = [I32, I32, I32, ctypes.POINTER(SZ)]
@@ -111,7 +112,8 @@ def lib():
                           "dreams_visual_importance_workspace_size", "dreams_visual_importance", "dreams_visual_topk",
                           "dreams_visual_gather", "dreams_workspace_status", "dreams_tree_verify_attn_splits",
                           "dreams_tree_verify_attn_noalloc", "dreams_set_wait_limit", "dreams_prefill_attn_stats",
-                          "dreams_prefill_attn_entropy_mean", "dreams_prefill_visual_importance"):
+                          "dreams_prefill_attn_entropy_mean", "dreams_prefill_visual_importance",
+                          "dreams_prefill_visual_importance_workspace_size"):
                     getattr(L, f).restype = ctypes.c_int
                 _lib = L
     return _lib
@@ -336,6 +338,14 @@ def prefill_attn_entropy_mean(entropy: torch.Tensor, prompt_len: torch.Tensor, a
     return ae
 
 
+def prefill_visual_importance_workspace_size(batch: int, num_kv_heads: int, vis_count: int) -> int:
+    """Bytes that hold the partial sums of every piece a prompt's rows are cut into; a workspace of
+    visual_importance_workspace_size bytes serves too, with fewer pieces."""
+    n = ctypes.c_size_t(0)
+    _check(lib().dreams_prefill_visual_importance_workspace_size(batch, num_kv_heads, vis_count, ctypes.byref(n)))
+    return n.value
+
+
 def prefill_visual_importance(q: torch.Tensor, k_cache: torch.Tensor, prompt_len: torch.Tensor, lse: torch.Tensor,
                               vis_begin: int, vis_count: int, scale: Optional[float] = None,
                               importance: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
@@ -352,10 +362,9 @@ def prefill_visual_importance(q: torch.Tensor, k_cache: torch.Tensor, prompt_len
         importance = torch.empty((B, vis_count), dtype=torch.float32, device=dev)
     else:
         _need(importance, "importance", torch.float32, dev)
-    nbytes = visual_importance_workspace_size(B, k_cache.shape[1], vis_count)
     st = _stream(stream)
     if workspace is None:
-        workspace = _workspace("visual", nbytes, dev, st)
+        workspace = _workspace("visual", prefill_visual_importance_workspace_size(B, k_cache.shape[1], vis_count), dev, st)
     desc = prefill_desc(q, k_cache, scale)
     _check(lib().dreams_prefill_visual_importance(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(prompt_len),
                                                   _ptr(lse), vis_begin, vis_count, _ptr(importance), _ptr(workspace),

@@ -88,6 +88,34 @@ def test_prefill_parity(dev, case):
     check(p, dev, "prefill %s" % (case,))
 
 
+EDGES = [  # edges of the 128-row workgroups, the 32-row waves and the 64-key stages; pieces of a head's rows
+    (2, 3, 3, 64, (127, 129), 0, 127),
+    (3, 2, 1, 128, (33, 64, 97), 1, 96),
+    (1, 14, 2, 128, (513,), 30, 470),         # 7 heads a KV head: 16 pieces, cut inside heads
+    (2, 16, 2, 64, (640, 385), 5, 300),
+]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[str(c[:5]) for c in EDGES])
+def test_prefill_edges_and_pieces(dev, case):
+    B, Hq, Hkv, D, lens, vb, vc = case
+    p = W.make_prompt(B, Hq, Hkv, D, lens, vb, vc, seed=66)
+    check(p, dev, "prefill edges %s" % (case,))
+    # the smallest workspace (one piece), one that holds three, and garbage in the partial sums' place
+    ref = run_oracle(p)[2]
+    q, k, pl = to_dev(p.q, dev, True), to_dev(p.k_cache, dev, True), to_dev(p.prompt_len, dev)
+    lse, _ = dreams.prefill_attn_stats(q, k, pl)
+    least = dreams.visual_importance_workspace_size(B, Hkv, vc)
+    assert dreams.prefill_visual_importance_workspace_size(B, Hkv, vc) >= least
+    for nbytes in (least, 65536 + 3 * (least - 65536) + 4):
+        ws = torch.full((nbytes,), 0x7f, dtype=torch.uint8, device=dev)
+        ws[:65536] = 0
+        imp = dreams.prefill_visual_importance(q, k, pl, lse, vb, vc, workspace=ws)
+        torch.cuda.synchronize()
+        assert importance_error(imp.cpu().numpy().astype(np.float64), ref)[1]
+        assert not ws[:65536].cpu().numpy().any()
+
+
 def test_prefill_empty_prompt(dev):
     # a sequence with no prompt: every row -inf / 0, importance 0, and it does not count in AE
     p = W.make_prompt(2, 4, 4, 128, (0, 90), 0, 80, num_rows=96, seed=62)
