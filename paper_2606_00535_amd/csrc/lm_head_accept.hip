@@ -336,7 +336,13 @@ __global__ __launch_bounds__(64 * WR * WN) void lm_head_argmax_big_kernel(LmHead
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;
   const int wr = wave / WN, wn = wave % WN;   // this wave's 64 rows and WB vocabulary entries of the tile
-  const int mt = blockIdx.x % a.mtiles, nt = blockIdx.x / a.mtiles;
+  // Consecutive workgroup ids go round-robin over the 8 XCDs: the row tiles of one vocabulary tile are the ids n,
+  // n + 8, ..., which share the tile's weights in one XCD's L2.  (With the row tiles on consecutive ids every XCD
+  // read every weight; the clock is held down by power at these shapes, and moving less raises it: 2048 rows x
+  // 152064 x 3584 took 1823 us so, 1743 us now, with as many cycles.)
+  const int slot = blockIdx.x >> 3;
+  const int mt = slot % a.mtiles, nt = (slot / a.mtiles) * 8 + (blockIdx.x & 7);
+  if (nt >= a.ntiles) return;
   const int n0 = nt * BN, m0 = mt * BIG_M;
   const int H = a.H, nstages = H / SK;
 
@@ -446,10 +452,11 @@ __global__ __launch_bounds__(64 * WR * WN) void lm_head_argmax_big_kernel(LmHead
 hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)((long long)a.ntiles * a.mtiles));
   static_assert(kLmTileBig == 256, "four vocabulary waves");
+  const dim3 big_grid((unsigned)((a.ntiles + 7LL) / 8 * 8 * a.mtiles));
   if (a.rows == kLmBigRows)
-    hipLaunchKernelGGL((lm_head_argmax_big_kernel<4, 4, 4, 64, 2>), grid, dim3(1024), 0, stream, a);
+    hipLaunchKernelGGL((lm_head_argmax_big_kernel<4, 4, 4, 64, 2>), big_grid, dim3(1024), 0, stream, a);
   else if (a.rows == kLmMidRows)
-    hipLaunchKernelGGL((lm_head_argmax_big_kernel<2, 4, 4, 64, 3>), grid, dim3(512), 0, stream, a);
+    hipLaunchKernelGGL((lm_head_argmax_big_kernel<2, 4, 4, 64, 3>), big_grid, dim3(512), 0, stream, a);
   else {
     static bool configured = false;
     if (!configured) {
