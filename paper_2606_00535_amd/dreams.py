@@ -125,17 +125,22 @@ def _check(status: int):
         raise DreamsError(status, msg)
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# Addresses and streams go to the library as plain integers (every prototype declares them as pointers, so ctypes
+# converts them): boxing each in a c_void_p and the current stream in a torch.cuda.Stream took 3 of a small call's 13 us.
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _need(t: torch.Tensor, name: str, dtype, device=None, ndim=None):
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous()
+            and (ndim is None or t.dim() == ndim) and (device is None or t.device == device)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.dtype != dtype:
@@ -155,10 +160,10 @@ _ws = {}
 _ws_lock = threading.Lock()
 
 
-def _workspace(kind: str, nbytes: int, device: torch.device, stream) -> Optional[torch.Tensor]:
+def _workspace(kind: str, nbytes: int, device: torch.device, stream: int) -> Optional[torch.Tensor]:
     if nbytes == 0:
         return None
-    key = (kind, device.index, stream.value if stream.value else 0)
+    key = (kind, device.index, stream)
     with _ws_lock:
         t = _ws.get(key)
         if t is None or t.numel() < nbytes:
