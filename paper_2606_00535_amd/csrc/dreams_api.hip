@@ -83,7 +83,8 @@ struct AttnPlan {
 constexpr long long kMaxSetCounters = (long long)kMaxCounters / 2;
 
 constexpr int kPieceMinKeys = 128;   // keys per piece of the key axis, at least
-constexpr int kPlanPieceKeys = 384;  // keys per piece, at least, where the library chooses the pieces
+constexpr int kPlanPieceKeys = 384;  // keys per piece, at least, where the library chooses the pieces ...
+constexpr int kFineSplits = 16;      // ... except up to this many while every workgroup has a compute unit of its own
 
 constexpr int kMaxSplitsRequest = 4096;
 
@@ -113,7 +114,48 @@ dreams_status_t check_attn_desc(const dreams_attn_desc_t* d) {
   return DREAMS_OK;
 }
 
-dreams_status_t plan_attn(const dreams_attn_desc_t* d, AttnPlan* p) {
+// Pieces of the key axis where the library chooses them: at most one workgroup per resident slot (one or two per
+// compute unit, as the configuration's LDS allows), in pieces of at least kPlanPieceKeys keys: shorter pieces cost more
+// in their fixed start and merge than they gain in parallel streams (llava7b_layer: 8 pieces of 400 keys 18.5 us, 16 of
+// 200 keys 20.4 us).  With more workgroups than slots: a last round of workgroups that fills less than half of the chip
+// cannot keep the memory busy, so the key axis is cut until it does (or the rounds come out whole).
+int coarse_splits(long long wgs, long long slots, int n_keys) {
+  if (wgs < slots) {
+    const long long by_len = n_keys / kPlanPieceKeys;
+    const long long s = slots / wgs < by_len ? slots / wgs : by_len;
+    return s > 1 ? (int)s : 1;
+  }
+  int splits = 1;
+  while (splits < 4 && (wgs * splits) % slots != 0 && (wgs * splits) % slots < slots / 2) ++splits;
+  return splits;
+}
+
+// The same for one XCD, which holds all workgroups of a unit: `wgs` workgroups on `cus` compute units of wpc slots.
+// Fewer slots than the whole chip's when there are under 8 units (28 heads on 4 KV heads x 8000 keys, 100 nodes: 21
+// pieces, two rounds on each of 4 XCDs, 76.7 us; 10 pieces 38.4 us).  While the pieces leave a compute unit to each
+// workgroup, they pay down to kPieceMinKeys keys, up to kFineSplits of them (32 heads x 1000 keys, 60 nodes: 2 pieces
+// 19.1 us, 8 pieces 12.2 us; 8 heads of 64 on 2 x 2000: 5 pieces 16.8 us, 16 pieces 12.5 us; 32 on 8 x 3000, 8 nodes:
+// 16 pieces 10.6 us, 24 pieces 11.7 us).
+int fine_splits(long long wgs, long long cus, int wpc, int n_keys) {
+  const long long coarse_len = n_keys / kPlanPieceKeys, fine_len = (n_keys + kPieceMinKeys - 1) / kPieceMinKeys;
+  const long long coarse = cus * wpc / wgs < coarse_len ? cus * wpc / wgs : coarse_len;
+  long long fine = cus / wgs < fine_len ? cus / wgs : fine_len;
+  if (fine > kFineSplits) fine = kFineSplits;
+  const long long s = coarse > fine ? coarse : fine;
+  return s > 1 ? (int)s : 1;
+}
+
+size_t attn_partial_bytes(AttnPlan* p, int splits, int head_dim) {
+  const size_t rows = (size_t)p->units * p->row_groups * splits * p->rows_per_wg;
+  p->o_off = kCounterBytes;
+  p->ml_off = p->o_off + align_up(rows * head_dim * 2, 256);
+  p->e_off = p->ml_off + align_up(rows * 2 * sizeof(float), 256);
+  return p->e_off + align_up(rows * sizeof(float), 256);
+}
+
+// workspace_bytes: what a call brings (the size query plans for as much as is needed).  A call that brings less than
+// the finer pieces need gets the coarse ones, where it holds those.
+dreams_status_t plan_attn(const dreams_attn_desc_t* d, AttnPlan* p, size_t workspace_bytes = SIZE_MAX) {
   dreams_status_t st = check_attn_desc(d);
   if (st != DREAMS_OK) return st;
   *p = AttnPlan{};
@@ -133,20 +175,16 @@ dreams_status_t plan_attn(const dreams_attn_desc_t* d, AttnPlan* p) {
     int cus = 0;
     st = device_cus(&cus);
     if (st != DREAMS_OK) return st;
-    // At most one workgroup per resident slot (one or two per compute unit, as the configuration's LDS allows),
-    // in pieces of at least kPlanPieceKeys keys: shorter pieces cost more in their fixed start and merge than
-    // they gain in parallel streams (llava7b_layer: 8 pieces of 400 keys 18.5 us, 16 of 200 keys 20.4 us).
-    const long long slots = (long long)cus * tree_attn_bf16_wgs_per_cu(p->rows_per_wg);
-    const long long wgs = (long long)p->units * p->row_groups;
-    if (wgs < slots) {
-      splits = (int)(slots / wgs);
-      const int by_len = n_keys / kPlanPieceKeys;
-      if (splits > by_len) splits = by_len;
-    } else {
-      // More workgroups than slots: a last round of workgroups that fills less than half of the chip cannot
-      // keep the memory busy, so cut the key axis until it does (or the rounds come out whole).
-      splits = 1;
-      while (splits < 4 && (wgs * splits) % slots != 0 && (wgs * splits) % slots < slots / 2) ++splits;
+    const int wpc = tree_attn_bf16_wgs_per_cu(p->rows_per_wg);
+    splits = coarse_splits((long long)p->units * p->row_groups, (long long)cus * wpc, n_keys);
+    if (splits > kAttnMaxSplits) splits = kAttnMaxSplits;
+    // (a call of one piece stays one: pieces round their rows to bf16 once more)
+    const long long xcd_wgs = (p->units + 7LL) / 8 * p->row_groups, xcd_cus = cus / 8;
+    if (splits > 1 && xcd_wgs < xcd_cus * wpc) {
+      const int fine = fine_splits(xcd_wgs, xcd_cus, wpc, n_keys);
+      if (fine <= splits || attn_partial_bytes(p, fine, d->head_dim) <= workspace_bytes ||
+          attn_partial_bytes(p, splits, d->head_dim) > workspace_bytes)
+        splits = fine;
     }
   }
   if (splits > max_splits) splits = max_splits;
@@ -164,11 +202,7 @@ dreams_status_t plan_attn(const dreams_attn_desc_t* d, AttnPlan* p) {
     int stride = 16;
     while (stride > 2 && sets * stride > kMaxSetCounters) stride >>= 1;
     p->ctr_stride = stride;
-    const size_t rows = (size_t)sets * splits * p->rows_per_wg;
-    p->o_off = kCounterBytes;
-    p->ml_off = p->o_off + align_up(rows * d->head_dim * 2, 256);
-    p->e_off = p->ml_off + align_up(rows * 2 * sizeof(float), 256);
-    p->bytes = p->e_off + align_up(rows * sizeof(float), 256);
+    p->bytes = attn_partial_bytes(p, splits, d->head_dim);
   }
   return DREAMS_OK;
 }
@@ -291,7 +325,7 @@ dreams_status_t verify_attn(const dreams_attn_desc_t* desc, const void* q, const
   if (st != DREAMS_OK) return st;
   if (desc->batch == 0) return ok();
   AttnPlan p;
-  st = plan_attn(desc, &p);
+  st = plan_attn(desc, &p, workspace ? workspace_bytes : SIZE_MAX);
   if (st != DREAMS_OK) return st;
   if (p.bytes > 0) {
     if (!workspace) return fail(DREAMS_ERR_WORKSPACE, "workspace is NULL but %zu bytes are needed", p.bytes);

@@ -541,11 +541,19 @@ __global__ __launch_bounds__(64 * W, WPC * W / 4) void tree_attn_bf16_kernel(Att
     for (int rb = 0; rb < RB; ++rb) {
       // (NaN-propagating maximum: three-input instructions, no canonicalising of the products' results; a
       // score is never NaN, the rows past a sequence's end being zeroed)
-      // A chain, so that every step is one three-input maximum.
-      float x = vmax(vmax(s[rb][0][0], s[rb][0][1]), s[rb][0][2]);
-      x = vmax(vmax(x, s[rb][0][3]), s[rb][1][0]);
-      x = vmax(vmax(x, s[rb][1][1]), s[rb][1][2]);
-      lmax[rb] = c_scale * vmax(x, s[rb][1][3]);
+      // Two row blocks: a chain, so that every step is one three-input maximum (four instructions instead of six:
+      // head_dim 64 with entropies 18.05 -> 17.65 us); one row block: a tree, which is shorter (18.8 against 18.9 us).
+      float x;
+      if constexpr (RB > 1) {
+        x = vmax(vmax(s[rb][0][0], s[rb][0][1]), s[rb][0][2]);
+        x = vmax(vmax(x, s[rb][0][3]), s[rb][1][0]);
+        x = vmax(vmax(x, s[rb][1][1]), s[rb][1][2]);
+        x = vmax(x, s[rb][1][3]);
+      } else {
+        x = vmax(vmax(vmax(s[rb][0][0], s[rb][0][1]), vmax(s[rb][0][2], s[rb][0][3])),
+                 vmax(vmax(s[rb][1][0], s[rb][1][1]), vmax(s[rb][1][2], s[rb][1][3])));
+      }
+      lmax[rb] = c_scale * x;
       grow |= lmax[rb] > m_run[rb] + kLazyLog2;
     }
     // The reference maximum m only moves when some score exceeds it by more than 2^8 (the exponentials then

@@ -384,6 +384,42 @@ def test_mask_input_matches_parent_and_empty_rows(dev):
 
 
 
+PIECE_CASES = [  # (B, D, Hq, Hkv, T, depth, branch, L): the library's own pieces
+    (1, 128, 8, 8, 16, 4, 3, 1500),      # one workgroup an XCD: as fine as 128 keys a piece
+    (1, 64, 4, 1, 30, 4, 3, 2300),       # one unit, so one XCD only; 16 pieces
+    (1, 128, 7, 1, 100, 8, 6, 2500),     # six row groups on one XCD: two workgroups a compute unit
+    (1, 128, 16, 16, 60, 6, 4, 800),     # two units an XCD
+    (2, 128, 24, 12, 9, 3, 3, 900),      # 24 units, ragged lengths
+    (1, 128, 4, 4, 60, 6, 4, 700),       # one piece, as with coarse pieces
+]
+
+
+@pytest.mark.parametrize("case", PIECE_CASES, ids=lambda c: "B%d_D%d_Hq%d_Hkv%d_T%d_L%d" % (c[0], c[1], c[2], c[3], c[4], c[7]))
+def test_library_chosen_pieces(dev, case):
+    B, D, Hq, Hkv, T, depth, br, L = case
+    wl = small_wl(batch=B, head_dim=D, num_q_heads=Hq, num_kv_heads=Hkv, num_nodes=T, depth=depth, max_branch=br, kv_len=L)
+    batch = W.make_batch(wl, with_logits=False, kv_lens=[L, 150][:B])
+    q, k, v, kv, par = layer_tensors(batch, 0, dev)
+    auto = splits_of(q, k, max_kv_len=L)
+    out, lse = dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=L)
+    torch.cuda.synchronize()
+    check_bf16(out, lse, batch, 0, "library's pieces %s" % (case,), splits=auto)
+    out2, lse2 = dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=L, num_splits=auto)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16)) and torch.equal(lse, lse2)
+    # a workspace that holds only the coarse pieces (at least 384 keys each) gets those
+    coarse = max(1, (L + T) // 384)
+    if 1 < coarse < auto:
+        need = dreams.tree_verify_attn_workspace_size(dreams.attn_desc(q, k, num_splits=coarse, max_kv_len=L))
+        small = torch.zeros(need, dtype=torch.uint8, device=dev)
+        out3, lse3 = dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=L, workspace=small)
+        out4, lse4 = dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=L, num_splits=coarse)
+        torch.cuda.synchronize()
+        assert torch.equal(out3.view(torch.int16), out4.view(torch.int16)) and torch.equal(lse3, lse4)
+        with pytest.raises(dreams.DreamsError):
+            dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=L, workspace=small[:need - 256])
+
+
 @pytest.mark.parametrize("splits", [2, 4, 7])
 def test_pieces_cut_per_sequence_length(dev, splits):
     # several sequences of very different lengths (one with no prefix): each sequence's key axis is cut into
