@@ -261,7 +261,6 @@ struct LmHeadArgs {
   int B, T, H, V, M, ntiles, mtiles;
   int rows;                // rows per workgroup: kLmTile (kLmTileSmall vocabulary entries each), else kLmMidRows or
                            // kLmBigRows (kLmTileBig entries each)
-  int cus;                 // compute units of the device (up to kLmTile rows: workgroups, at most)
 };
 
 hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream);

@@ -155,10 +155,10 @@ __global__ __launch_bounds__(FIN_THREADS) void lm_head_finish_kernel(LmHeadArgs 
 // weight rows into its ring slot (two wave-wide LDS-DMA copies of 8 rows x 128 bytes) and loads 16 bytes of the
 // tile's hidden rows per thread into registers (thread t: row t / 8, chunk t % 8); a stage's hidden rows are
 // written to one of three shared LDS buffers one stage before they are used, and a barrier publishes them.
-// Every vector-memory operation of the loop is issued by inline assembly and waited for by exact count (a tile's few
-// stores among them only make a wait stricter): a stage is issued DW - 1 stages ahead, and at stage s the wave waits
-// for stage s + 1, leaving DW - 2 stages of copies in flight.  The 16-byte chunk c of a row r sits at position
-// c ^ (r % 8) of its 128-byte LDS row, so that the 16 rows one operand read touches fall on distinct banks.
+// Every vector-memory operation of the loop is issued by inline assembly and waited for by exact count: a
+// stage is issued DW - 1 stages ahead, and at stage s the wave waits for stage s + 1, leaving DW - 2 stages of
+// copies in flight.  The 16-byte chunk c of a row r sits at position c ^ (r % 8) of its 128-byte LDS row, so
+// that the 16 rows one operand read touches fall on distinct banks.
 constexpr int LM_WAVES = kLmTileSmall / 16, LM_SK = 64, LM_DW = 8, LM_XBUF = 3;
 constexpr int LM_WSLOT = 16 * LM_SK * 2, LM_XSTAGE = kLmTile * LM_SK * 2;
 constexpr size_t LM_LDS = (size_t)LM_WAVES * LM_DW * LM_WSLOT + (size_t)LM_XBUF * LM_XSTAGE;
@@ -172,184 +172,152 @@ template <int N>
 __device__ __forceinline__ void wait_vm_tied(bf16x8& x) {
   asm volatile("s_waitcnt vmcnt(%1)" : "+v"(x) : "n"(N) : "memory");
 }
+
 __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArgs a) {
-  constexpr int DW = LM_DW, ROWS = kLmTile, MT = ROWS / 16;
-  static_assert(ROWS == 64 && LM_WAVES == 8, "64 rows; eight waves, each owning 16 vocabulary entries");
-  static_assert(LM_LDS + 2 * LM_WAVES * ROWS * 4 <= 160 * 1024, "LDS budget");
+  static_assert(kLmTile == 64 && LM_WAVES == 8, "64 rows; eight waves, each owning 16 vocabulary entries");
+  static_assert(LM_LDS + 2 * LM_WAVES * kLmTile * 4 <= 160 * 1024, "LDS budget");
   extern __shared__ __attribute__((aligned(1024))) char lm_lds[];
   char* wring = lm_lds;                                         // [wave][DW][16 rows x 128 B]
-  char* xs = lm_lds + (size_t)LM_WAVES * DW * LM_WSLOT;         // [3][64 rows x 128 B]
-  __shared__ float best_v[LM_WAVES][ROWS];
-  __shared__ int best_i[LM_WAVES][ROWS];
+  char* xs = lm_lds + (size_t)LM_WAVES * LM_DW * LM_WSLOT;      // [3][64 rows x 128 B]
+  __shared__ float best_v[LM_WAVES][kLmTile];
+  __shared__ int best_i[LM_WAVES][kLmTile];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;
-  const int H = a.H, nstages = H / LM_SK, quarter = nstages / 4;
+  // the row tiles of one vocabulary tile are consecutive workgroups, so its weights are fetched from HBM once
+  // and found in the caches by the others
+  const int mt = blockIdx.x % a.mtiles, nt = blockIdx.x / a.mtiles;
+  const int n0 = nt * kLmTileSmall + 16 * wave, m0 = mt * kLmTile;
+  const int H = a.H, nstages = H / LM_SK;
   // weight copies: copy j brings rows 8 j + lane / 8 of the wave's 16 (clamped past the vocabulary: their
   // results are discarded), chunk position lane % 8, i.e. the row's chunk (lane % 8) ^ (row % 8)
   const int crow = lane >> 3, cchunk = (lane & 7) ^ (crow & 7);
-  const uint32_t wring_lds = __builtin_amdgcn_readfirstlane(lds_addr(wring + (size_t)wave * DW * LM_WSLOT));
+  const __bf16* wsrc0 = a.weight + (size_t)min(n0 + crow, a.V - 1) * H + 8 * cchunk;
+  const __bf16* wsrc1 = a.weight + (size_t)min(n0 + 8 + crow, a.V - 1) * H + 8 * cchunk;
+  const uint32_t wring_lds = __builtin_amdgcn_readfirstlane(lds_addr(wring + (size_t)wave * LM_DW * LM_WSLOT));
   // hidden piece of this thread: row t / 8 (clamped past the rows), chunk t % 8, written at c ^ (r % 8)
   const int xr = threadIdx.x >> 3, xc = threadIdx.x & 7;
-  const __bf16* xsrc = a.hidden + (size_t)min(xr, a.M - 1) * H + 8 * xc;
+  const __bf16* xsrc = a.hidden + (size_t)min(m0 + xr, a.M - 1) * H + 8 * xc;
   const int xw = xr * 128 + ((xc ^ (xr & 7)) << 4);
 
-  // A workgroup takes vocabulary tiles blockIdx, blockIdx + gridDim, ... as one stream of stages: the next tile's
-  // copies are in flight while a tile's rows are reduced.  (A workgroup per tile paid its start and its drain once per
-  // tile: 228 us at 60 rows x 152064 x 3584, 213 us so; 60 x 100000 x 2048 102 and 95 us.)
-  // The hidden axis in quarters: a tile starts at quarter nt % 4 and wraps round, so that the workgroups, which keep
-  // in step, do not all read the same 1 KB of their 8 KB rows at a time (which the memory channels serve unevenly:
-  // 54.8 us with all of them from quarter 0, 44.3 us so, at 60 rows x 32000 x 4096, 5.9 TB/s; level where a row is not
-  // a multiple of 4 KB).  Each quarter has its
-  // own sums, added in one order wherever the tile started, so equal weight rows of different tiles still tie.
-  int ahead_nt = blockIdx.x, ahead_left = nstages, ahead_k = (ahead_nt & 3) * quarter;   // the next stage to issue
-  const __bf16 *wsrc0, *wsrc1;
-  auto weights_of = [&](int nt) {
-    const int n0 = nt * kLmTileSmall + 16 * wave + crow;
-    wsrc0 = a.weight + (size_t)min(n0, a.V - 1) * H + 8 * cchunk;
-    wsrc1 = a.weight + (size_t)min(n0 + 8, a.V - 1) * H + 8 * cchunk;
-  };
-  weights_of(ahead_nt);
-  bf16x8 hv[DW];
-  auto issue = [&](int slot) {
-    const int k = ahead_k * LM_SK;
+  // The hidden axis in quarters: a workgroup starts at quarter nt % 4 and wraps round, so that the workgroups,
+  // which keep in step, do not all read the same 1 KB of their 8 KB rows at a time (which the memory channels
+  // serve unevenly: 54.8 us with all of them from quarter 0, 44.3 us so, at 60 rows x 32000 x 4096, 5.9 TB/s).  Each quarter has its own sums,
+  // added in one order wherever the workgroup started, so equal weight rows of different tiles still tie.
+  const int quarter = nstages / 4, start = (nt & 3) * quarter;
+  bf16x8 hv[LM_DW];
+  auto issue = [&](int slot, int s) {
+    int ks = min(s, nstages - 1) + start;   // (stages past the end repeat the last one, unused)
+    if (ks >= nstages) ks -= nstages;
+    const int k = ks * LM_SK;
     const uint32_t dst = wring_lds + slot * LM_WSLOT;
     copy16_to_lds<true>(dst, wsrc0 + k);
     copy16_to_lds<true>(dst + 1024, wsrc1 + k);
     load16_async(hv[slot], xsrc + k);
-    if (ahead_left > 1) {
-      --ahead_left;
-      if (++ahead_k == nstages) ahead_k = 0;
-    } else if (ahead_nt + (int)gridDim.x < a.ntiles) {   // (past the last tile its last stage is issued again, unused)
-      ahead_nt += (int)gridDim.x;
-      ahead_left = nstages;
-      ahead_k = (ahead_nt & 3) * quarter;
-      weights_of(ahead_nt);
-    }
   };
-  // the hidden rows of a slot, once landed, into their buffer
-  auto publish = [&](int slot, int s) {
-    wait_vm_tied<3 * (DW - 2)>(hv[slot]);
-    *(bf16x8*)(xs + (size_t)(s % LM_XBUF) * LM_XSTAGE + xw) = hv[slot];
-  };
-  // The current quarter's sums, and those of the quarters before it: q0 + q1, then q2 (started on an even one), or q0,
-  // then q1 + q2 (on an odd one), which gives (q0 + q1) + (q2 + q3) in the row's own order in the end either way.
-  f32x4 acc[MT], d0[MT], d1[MT];
+  f32x4 acc[4], done[3][4];   // the current quarter's sums; those of the quarters before it, the latest first
 #pragma unroll
-  for (int r = 0; r < MT; ++r) acc[r] = d0[r] = d1[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-  int nt = blockIdx.x, done_stages = 0;   // the tile whose stages are computed, and how many of them are
-  int boundary = quarter, past = 0;   // the next quarter's first stage; quarters finished
+  for (int r = 0; r < 4; ++r) acc[r] = done[0][r] = done[1][r] = done[2][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int boundary = quarter;   // the next quarter's first stage
   auto compute = [&](int slot, int s) {
-    if (done_stages == boundary) {   // (the last products into acc were issued a barrier ago)
+    if (s == boundary) {   // (the last products into acc were issued a barrier ago)
       boundary += quarter;
-      ++past;
-      const bool first = past == 1 || (past == 2 && !(nt & 1));
 #pragma unroll
-      for (int r = 0; r < MT; ++r) {   // (selects: a branch would put the two arrays in memory)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          d0[r][e] += first ? acc[r][e] : 0.f;
-          d1[r][e] += first ? 0.f : acc[r][e];
-        }
+      for (int r = 0; r < 4; ++r) {
+        done[2][r] = done[1][r];
+        done[1][r] = done[0][r];
+        done[0][r] = acc[r];
         acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
-    const char* wst = wring + ((size_t)wave * DW + slot) * LM_WSLOT;
+    const char* wst = wring + ((size_t)wave * LM_DW + slot) * LM_WSLOT;
     const char* xst = xs + (size_t)(s % LM_XBUF) * LM_XSTAGE;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       const int c = 4 * ks + quad;
       const bf16x8 wa = *(const bf16x8*)(wst + col * 128 + ((c ^ (col & 7)) << 4));
-      bf16x8 xb[MT];
+      bf16x8 xb[4];
 #pragma unroll
-      for (int r = 0; r < MT; ++r) xb[r] = *(const bf16x8*)(xst + (16 * r + col) * 128 + ((c ^ (col & 7)) << 4));
+      for (int r = 0; r < 4; ++r) xb[r] = *(const bf16x8*)(xst + (16 * r + col) * 128 + ((c ^ (col & 7)) << 4));
 #pragma unroll
-      for (int r = 0; r < MT; ++r) acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xb[r], acc[r], 0, 0, 0);
+      for (int r = 0; r < 4; ++r) acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xb[r], acc[r], 0, 0, 0);
     }
   };
-  // a tile's stages are done: every row's best over its entries
-  auto reduce = [&]() {
-    const int n0 = nt * kLmTileSmall + 16 * wave;
 #pragma unroll
-    for (int r = 0; r < MT; ++r) {
-      acc[r] = (nt & 1) ? (acc[r] + d0[r]) + d1[r] : d0[r] + (d1[r] + acc[r]);
-    }
-    // lane (col, quad) of wave w: rows 16 r + col, vocabulary entries n0 + 4 quad + e
-#pragma unroll
-    for (int r = 0; r < MT; ++r) {
-      float v = -INFINITY;
-      int x = INT_MAX;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = n0 + 4 * quad + e;
-        if (n < a.V && (acc[r][e] > v || x == INT_MAX)) {
-          v = acc[r][e];
-          x = n;
-        }
-      }
-#pragma unroll
-      for (int off = 16; off <= 32; off <<= 1) {
-        const float v2 = __shfl_xor(v, off);
-        const int x2 = __shfl_xor(x, off);
-        if (better(v2, x2, v, x)) {
-          v = v2;
-          x = x2;
-        }
-      }
-      if (quad == 0) {
-        best_v[wave][16 * r + col] = v;
-        best_i[wave][16 * r + col] = x;
-      }
-    }
-    barrier_lds();
-    // each row's best over the tile's sub-tiles, in vocabulary order
-    if (threadIdx.x < ROWS && (int)threadIdx.x < a.M) {
-      const int row = threadIdx.x;
-      float v = best_v[0][row];
-      int x = best_i[0][row];
-#pragma unroll
-      for (int w = 1; w < LM_WAVES; ++w)
-        if (better(best_v[w][row], best_i[w][row], v, x)) {
-          v = best_v[w][row];
-          x = best_i[w][row];
-        }
-      const size_t p = (size_t)row * a.ntiles + nt;
-      a.part_val[p] = v;
-      a.part_idx[p] = x;
-    }
-#pragma unroll
-    for (int r = 0; r < MT; ++r) acc[r] = d0[r] = d1[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-    nt += (int)gridDim.x;
-    done_stages = past = 0;
-    boundary = quarter;
-  };
-#pragma unroll
-  for (int j = 0; j < DW - 1; ++j) issue(j);
-  publish(0, 0);
+  for (int j = 0; j < LM_DW - 1; ++j) issue(j, j);
+  wait_vm_tied<3 * (LM_DW - 2)>(hv[0]);   // stage 0 has landed
+  *(bf16x8*)(xs + xw) = hv[0];
   // Stage s: its slot's registers and ring slot take stage s + DW - 1 (the slot held stage s - 1, whose
   // weights were read by this wave's products and whose hidden rows went to LDS before); stage s + 1 lands and
   // its hidden rows go to their LDS buffer; the barrier publishes them and retires every wave's reads of the
-  // buffer stage s + 2 will take; then stage s is computed.  A tile has a multiple of 4 stages, so it ends only at
-  // every fourth of the unrolled ones.
-  static_assert(DW % 4 == 0 && kLmHiddenMultiple == 4 * LM_SK, "tiles end at every fourth stage");
-  for (int s0 = 0; nt < a.ntiles; s0 += DW) {
+  // buffer stage s + 2 will take; then stage s is computed.
+  for (int s0 = 0; s0 < nstages; s0 += LM_DW) {
 #pragma unroll
-    for (int j = 0; j < DW; ++j) {
+    for (int j = 0; j < LM_DW; ++j) {
       const int s = s0 + j;
-      issue((j + DW - 1) % DW);
-      publish((j + 1) % DW, s + 1);
+      if (s >= nstages) break;
+      issue((j + LM_DW - 1) % LM_DW, s + LM_DW - 1);
+      wait_vm_tied<3 * (LM_DW - 2)>(hv[(j + 1) % LM_DW]);
+      *(bf16x8*)(xs + (size_t)((s + 1) % LM_XBUF) * LM_XSTAGE + xw) = hv[(j + 1) % LM_DW];
       barrier_lds();
       compute(j, s);
-      ++done_stages;
-      if (j % 4 == 3 && done_stages == nstages) {
-        reduce();
-        if (nt >= a.ntiles) break;
-      }
     }
   }
   // copies issued past the last stage land before the workgroup's LDS is released, loads before their registers are
   // used for anything else
+  asm volatile("s_waitcnt vmcnt(0)"
+               : "+v"(hv[0]), "+v"(hv[1]), "+v"(hv[2]), "+v"(hv[3]), "+v"(hv[4]), "+v"(hv[5]), "+v"(hv[6]), "+v"(hv[7])
+               :
+               : "memory");
+  static_assert(LM_DW == 8, "every load register is tied to the wait");
+  // (q0 + q1) + (q2 + q3) of the quarters in the row's own order; the first one taken was quarter nt % 4
 #pragma unroll
-  for (int j = 0; j < DW; ++j) wait_vm_tied<0>(hv[j]);
+  for (int r = 0; r < 4; ++r)
+    acc[r] = (nt & 1) ? (acc[r] + done[2][r]) + (done[1][r] + done[0][r])
+                      : (done[2][r] + done[1][r]) + (done[0][r] + acc[r]);
+
+  // lane (col, quad) of wave w: rows 16 r + col, vocabulary entries n0 + 4 quad + e
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float v = -INFINITY;
+    int x = INT_MAX;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = n0 + 4 * quad + e;
+      if (n < a.V && (acc[r][e] > v || x == INT_MAX)) {
+        v = acc[r][e];
+        x = n;
+      }
+    }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+      const float v2 = __shfl_xor(v, off);
+      const int x2 = __shfl_xor(x, off);
+      if (better(v2, x2, v, x)) {
+        v = v2;
+        x = x2;
+      }
+    }
+    if (quad == 0) {
+      best_v[wave][16 * r + col] = v;
+      best_i[wave][16 * r + col] = x;
+    }
+  }
+  __syncthreads();
+  // each row's best over the tile's sub-tiles, in vocabulary order
+  if (threadIdx.x < kLmTile && m0 + (int)threadIdx.x < a.M) {
+    const int row = threadIdx.x;
+    float v = best_v[0][row];
+    int x = best_i[0][row];
+#pragma unroll
+    for (int w = 1; w < LM_WAVES; ++w)
+      if (better(best_v[w][row], best_i[w][row], v, x)) {
+        v = best_v[w][row];
+        x = best_i[w][row];
+      }
+    const size_t p = (size_t)(m0 + row) * a.ntiles + nt;
+    a.part_val[p] = v;
+    a.part_idx[p] = x;
+  }
 }
 
 template <int WR, int WN, int TW, int SK, int STAGES>
@@ -482,12 +450,13 @@ __global__ __launch_bounds__(64 * WR * WN) void lm_head_argmax_big_kernel(LmHead
 }  // namespace
 
 hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)((long long)a.ntiles * a.mtiles));
   static_assert(kLmTileBig == 256, "four vocabulary waves");
-  const dim3 grid((unsigned)((a.ntiles + 7LL) / 8 * 8 * a.mtiles));
+  const dim3 big_grid((unsigned)((a.ntiles + 7LL) / 8 * 8 * a.mtiles));
   if (a.rows == kLmBigRows)
-    hipLaunchKernelGGL((lm_head_argmax_big_kernel<4, 4, 4, 64, 2>), grid, dim3(1024), 0, stream, a);
+    hipLaunchKernelGGL((lm_head_argmax_big_kernel<4, 4, 4, 64, 2>), big_grid, dim3(1024), 0, stream, a);
   else if (a.rows == kLmMidRows)
-    hipLaunchKernelGGL((lm_head_argmax_big_kernel<2, 4, 4, 64, 3>), grid, dim3(512), 0, stream, a);
+    hipLaunchKernelGGL((lm_head_argmax_big_kernel<2, 4, 4, 64, 3>), big_grid, dim3(512), 0, stream, a);
   else {
     static bool configured = false;
     if (!configured) {
@@ -496,8 +465,7 @@ hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream) {
       if (e != hipSuccess) return e;
       configured = true;
     }
-    hipLaunchKernelGGL(lm_head_argmax_kernel, dim3((unsigned)(a.ntiles < a.cus ? a.ntiles : a.cus)),
-                       dim3(64 * LM_WAVES), LM_LDS, stream, a);
+    hipLaunchKernelGGL(lm_head_argmax_kernel, grid, dim3(64 * LM_WAVES), LM_LDS, stream, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

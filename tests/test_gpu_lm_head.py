@@ -156,13 +156,6 @@ def test_equal_rows_of_different_tiles_tie(dev, H):
     assert np.all(am.cpu().numpy().reshape(-1)[prefers] == 50)
 
 
-@pytest.mark.parametrize("T,H,V", [(64, 256, 32769), (7, 1280, 33000), (60, 768, 70001)])
-def test_several_tiles_per_workgroup(dev, T, H, V):
-    """More vocabulary tiles than compute units (256): a workgroup's second and third tile, of 4, 20 and 12 stages
-    (every turn of the 8-slot ring), a last tile of one entry, workgroups with one tile less than others."""
-    run_case(dev, np.random.default_rng(V), 1, T, H, V, "tiles per workgroup: T=%d H=%d V=%d" % (T, H, V))
-
-
 def test_large_batch_sampled_rows(dev):
     """The gqa_long shape (16 sequences of 128 nodes, hidden 3584, vocabulary 152064): the oracle checks 96
     sampled rows' argmax; every sequence's path must follow the greedy rule on the kernel's tokens."""
