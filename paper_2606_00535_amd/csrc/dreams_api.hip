@@ -764,6 +764,8 @@ dreams_status_t dreams_tree_accept_lm_head(int32_t batch, int32_t num_nodes, int
   a.ntiles = p.ntiles;
   a.rows = p.rows;
   a.mtiles = (a.M + p.rows - 1) / p.rows;
+  st = device_cus(&a.cus);
+  if (st != DREAMS_OK) return st;
   hipError_t e = launch_lm_head_accept(a, stream);
   if (e != hipSuccess) return hip_fail(e, "LM head accept launch");
   return ok();

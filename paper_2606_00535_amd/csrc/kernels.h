@@ -261,6 +261,7 @@ struct LmHeadArgs {
   int B, T, H, V, M, ntiles, mtiles;
   int rows;                // rows per workgroup: kLmTile (kLmTileSmall vocabulary entries each), else kLmMidRows or
                            // kLmBigRows (kLmTileBig entries each)
+  int cus;                 // compute units of the device (up to kLmTile rows: whether the workgroups fill it)
 };
 
 hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream);

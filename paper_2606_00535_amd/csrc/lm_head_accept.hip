@@ -173,6 +173,7 @@ __device__ __forceinline__ void wait_vm_tied(bf16x8& x) {
   asm volatile("s_waitcnt vmcnt(%1)" : "+v"(x) : "n"(N) : "memory");
 }
 
+template <bool QUARTERS>
 __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArgs a) {
   static_assert(kLmTile == 64 && LM_WAVES == 8, "64 rows; eight waves, each owning 16 vocabulary entries");
   static_assert(LM_LDS + 2 * LM_WAVES * kLmTile * 4 <= 160 * 1024, "LDS budget");
@@ -199,15 +200,13 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   const __bf16* xsrc = a.hidden + (size_t)min(m0 + xr, a.M - 1) * H + 8 * xc;
   const int xw = xr * 128 + ((xc ^ (xr & 7)) << 4);
 
-  // The hidden axis in quarters: a workgroup starts at quarter nt % 4 and wraps round, so that the workgroups,
-  // which keep in step, do not all read the same 1 KB of their 8 KB rows at a time (which the memory channels
-  // serve unevenly: 54.8 us with all of them from quarter 0, 44.3 us so, at 60 rows x 32000 x 4096, 5.9 TB/s).  Each quarter has its own sums,
+  // QUARTERS: a workgroup starts at quarter nt % 4 of the hidden axis and wraps round; each quarter has its own sums,
   // added in one order wherever the workgroup started, so equal weight rows of different tiles still tie.
-  const int quarter = nstages / 4, start = (nt & 3) * quarter;
+  const int quarter = nstages / 4, start = QUARTERS ? (nt & 3) * quarter : 0;
   bf16x8 hv[LM_DW];
   auto issue = [&](int slot, int s) {
     int ks = min(s, nstages - 1) + start;   // (stages past the end repeat the last one, unused)
-    if (ks >= nstages) ks -= nstages;
+    if (QUARTERS && ks >= nstages) ks -= nstages;
     const int k = ks * LM_SK;
     const uint32_t dst = wring_lds + slot * LM_WSLOT;
     copy16_to_lds<true>(dst, wsrc0 + k);
@@ -219,7 +218,7 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   for (int r = 0; r < 4; ++r) acc[r] = done[0][r] = done[1][r] = done[2][r] = f32x4{0.f, 0.f, 0.f, 0.f};
   int boundary = quarter;   // the next quarter's first stage
   auto compute = [&](int slot, int s) {
-    if (s == boundary) {   // (the last products into acc were issued a barrier ago)
+    if (QUARTERS && s == boundary) {   // (the last products into acc were issued a barrier ago)
       boundary += quarter;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -271,7 +270,7 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   static_assert(LM_DW == 8, "every load register is tied to the wait");
   // (q0 + q1) + (q2 + q3) of the quarters in the row's own order; the first one taken was quarter nt % 4
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int r = 0; r < (QUARTERS ? 4 : 0); ++r)
     acc[r] = (nt & 1) ? (acc[r] + done[2][r]) + (done[1][r] + done[0][r])
                       : (done[2][r] + done[1][r]) + (done[0][r] + acc[r]);
 
@@ -449,6 +448,19 @@ __global__ __launch_bounds__(64 * WR * WN) void lm_head_argmax_big_kernel(LmHead
 // per row, then the next batch).
 }  // namespace
 
+template <bool QUARTERS>
+hipError_t launch_stream(const LmHeadArgs& a, dim3 grid, hipStream_t stream) {
+  auto kern = lm_head_argmax_kernel<QUARTERS>;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LM_LDS);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  hipLaunchKernelGGL(kern, grid, dim3(64 * LM_WAVES), LM_LDS, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)((long long)a.ntiles * a.mtiles));
   static_assert(kLmTileBig == 256, "four vocabulary waves");
@@ -458,14 +470,14 @@ hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream) {
   else if (a.rows == kLmMidRows)
     hipLaunchKernelGGL((lm_head_argmax_big_kernel<2, 4, 4, 64, 3>), big_grid, dim3(512), 0, stream, a);
   else {
-    static bool configured = false;
-    if (!configured) {
-      hipError_t e = hipFuncSetAttribute((const void*)lm_head_argmax_kernel,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)LM_LDS);
-      if (e != hipSuccess) return e;
-      configured = true;
-    }
-    hipLaunchKernelGGL(lm_head_argmax_kernel, grid, dim3(64 * LM_WAVES), LM_LDS, stream, a);
+    // Workgroups keep in step.  Where their rows are multiples of 4 KB apart and they fill most of the chip, all of
+    // them would read the same 1 KB of every row at a time, which the memory channels serve unevenly: they start at
+    // different quarters (60 rows x 32000 x 4096: 54.8 -> 44.3 us, 5.9 TB/s; 100000 x 2048: 125 -> 105 us).  Elsewhere
+    // that only costs (14 rows x 2496 x 1536 18.4 -> 19.7 us, 1 x 8000 x 4096 34.3 -> 36.3, 60 x 152064 x 3584
+    // 219 -> 228).
+    const hipError_t e = a.H % 2048 == 0 && 2LL * a.ntiles > a.cus ? launch_stream<true>(a, grid, stream)
+                                                                   : launch_stream<false>(a, grid, stream);
+    if (e != hipSuccess) return e;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
