@@ -203,6 +203,7 @@ constexpr int kSampledParts[] = {2048, 4096, 8192, 10240};
 constexpr int kSampledStreamPart = 8192;
 constexpr int kSampledMaxPieces = 64;       // pieces per row, at most: one wave reads all of their slots
 constexpr int kSampledRowCounter = 2;       // a row's words: its child word (64 bits), then its counter
+constexpr uint32_t kClusterLeft = 1u << 16; // a cluster's counter: pieces entered below, pieces left from here up
 constexpr int kSampledRowSlotBytes = 32;    // a piece's exchange slots
 constexpr int kSampledWalkSlotBytes = 64;
 

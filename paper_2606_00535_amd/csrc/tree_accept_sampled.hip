@@ -39,7 +39,8 @@
 // store and one load of latency, with no counter in between.  Slots alternate between two places: a piece
 // writes step s + 2 only after it has read every piece's step s + 1, which each wrote after reading step s.
 // A slot holds anything at entry; each piece clears its own and counts itself in on the cluster's counter, and
-// nobody reads a slot before that count is whole.  (A row of one piece has nothing to exchange.)  The row form
+// nobody reads a slot before that count is whole (the pieces that left are counted apart, so that it means what it
+// says also where others gave up and left early).  (A row of one piece has nothing to exchange.)  The row form
 // has slots for the statistics only: a child's residual mass is summed over the pieces by one atomic each, in
 // fixed point (units of 2^-51, so the sum does not depend on the order of arrival), with the arrivals above it
 // and the decision between them, and the pieces poll that word.
@@ -224,7 +225,7 @@ struct Piece {
   const SampledArgs& a;
   Shared& sh;
   const int b, j;
-  uint32_t* const counter;        // the cluster's counter: pieces entered, then pieces left
+  uint32_t* const counter;        // the cluster's counter: pieces entered and (from kClusterLeft up) pieces left
   uint64_t* const slots;          // [chunks][SLOTS]
   uint32_t step = 0;
   int n = 0;                      // the row's node
@@ -291,7 +292,8 @@ struct Piece {
                                                 (l == N - 1 && bit ? kKeptBit : 0u));
     if (step == 1)   // every piece has cleared its slots
       wait_until([&] {
-        return __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)a.chunks;
+        return (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kClusterLeft - 1)) ==
+               (uint32_t)a.chunks;
       });
     const uint64_t* from = slots + min(l, a.chunks - 1) * SLOTS + at;
     bool kept = false;
@@ -512,8 +514,9 @@ struct Piece {
       } else {
         if (tid == 0) store_d(a.mass + (rb + c) * a.chunks + j, z);
         if (last) wait_vector_memory();   // (the piece's masses are stored before its last arrival)
-        // A piece's mass is at most 1 (up to rounding), a row's below 2, so that the decision's bit is free; after
-        // a wait gave up it is meaningless and counts as 0, so that it can never carry into the arrivals.
+        // A piece's mass is at most 1 (up to rounding), a row's below 2, so that the decision's bit is free.  After
+        // its wait gave up a piece's mass is meaningless and counts as 0; the others have read the statistics of
+        // every piece, so theirs are parts of a sum of at most 1: none can carry into the arrivals.
         const double zc = sh.gave_up ? 0.0 : fmin(fmax(z, 0.0), 2.0);
         const uint64_t add = (1ull << kArrivalShift) + (uint64_t)rint(zc * kFixScale) + (keep ? kKeptWordBit : 0);
         uint64_t* word = (uint64_t*)(a.row_ctr + (rb + c) * a.row_stride);
@@ -631,8 +634,8 @@ struct Piece {
 
   // (thread 0, once this piece's stores are done) counts this piece out; true in the cluster's last one
   __device__ __forceinline__ bool leave() {
-    return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-           (uint32_t)(2 * a.chunks - 1);
+    return __hip_atomic_fetch_add(counter, kClusterLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kClusterLeft ==
+           (uint32_t)(a.chunks - 1);
   }
 };
 
