@@ -526,20 +526,33 @@ dreams_status_t dreams_tree_accept(int32_t batch, int32_t num_nodes, int32_t voc
 }
 
 // ------------------------------------------------------------------------------------- sampled acceptance
-// Row-form workgroups (pieces of 4096 entries of every row) beyond which the walk form is taken.  The row form's time
-// grows with its workgroups, the walk form's with the rows visited (about 6 us each; trees 4 to 8 deep, drafts
-// that follow the target): 576 workgroups (8 x 9 rows of 32000) 23.6 against 44 us, 960 (2 x 60 of 32000) 35.6
-// against 30.5, 1440 44.5 against 32.7, 2048 (16 x 128 of 1000) 46.5 against 31, 2280 (60 of 152064) 82 against 42.
-// (A chain of dozens of drafts that are all kept is the walk form's worst case.)
+// Row-form workgroups (pieces of 4096 entries of every row) beyond which rows that the walk does not visit are left out
+// where the tree allows it.  576 workgroups (8 x 9 rows of 32000): 23.6 us by rows, 44 us walked; 960 (2 x 60 of
+// 32000): 35.6 and 30.5; 1440: 44.5 and 32.7; 2280 (60 of 152064): 82 and 42.
 constexpr long long kSampledWalkFrom = 1024;
 // Vocabularies that one workgroup walks alone: no exchange at all (128 nodes x 1000 entries: 2 us a row).
 constexpr int kSampledWalkAlone = 8192;
 constexpr long long kSampledMaxVocab = 1ll << 23;
 
 struct SampledPlan {
-  int walk, part, sub_pieces, chunks, row_stride;
+  int form, clusters, walk_chunks, max_visits, part, sub_pieces, chunks, row_stride;
   size_t row_base, slot_off, mass_off, flag_off, bytes;
 };
+
+// Nodes of the longest path that is walked.  How far a walk goes is not known before it ends, and the host does not see
+// the tree: those kernels read its paths and walk only while the longest one, were all of it kept, would cost about
+// what all rows cost, which is 20 us and 0.028 us a workgroup; a node visited costs 6.2 us and what its piece takes
+// longer in wide rows.  Chains of which every draft is kept, walked, by rows, and by rows before there was a walk:
+// 4 x 60 of 32000 383, 71, 69 us; 8 x 60 of 32000 386, 117, 114; 60 of 152064 483, 95, 97; 2 x 128 of 32000 818, 78,
+// 77; 128 of 152064 1023, 190, 125; 4 x 128 of 152064 1085, 740, 430.  Trees up to 8 deep take what they took when
+// every call was walked (25 to 100 us, within 5 %).
+// Vocabularies beyond 64 pieces of 4096 entries are always walked (24 kept drafts of 300000 entries 253 us, 8 of 700000
+// 231 us; 107 and 121 us before there was a walk).
+int sampled_max_visits(long long wgs, int V) {
+  const double most = (20.0 + 0.028 * (double)wgs) / (6.2 + V / 85000.0);
+  return most < kMaxNodes ? (int)most : kMaxNodes;
+}
+constexpr int kSampledEitherWgs = 2;   // row-form workgroups a compute unit holds where either form may be taken
 
 // cus: compute units of the device (the workspace's size does not depend on it)
 dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPlan* p) {
@@ -569,13 +582,36 @@ dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPl
   p->flag_off = take(rows * 2 * sizeof(int32_t));
   p->bytes = off;
 
+  const long long room = (long long)(p->flag_off - p->slot_off), wgs = (long long)rows * pieces(kSampledRowPart);
   long long part = kSampledRowPart, sub = 1;
-  const bool walk = (long long)rows * pieces(part) > kSampledWalkFrom || pieces(part) > kSampledMaxPieces;
+  p->form = kSampledRows;
+  p->clusters = T;
+  if (wgs > kSampledWalkFrom || pieces(part) > kSampledMaxPieces) {
+    p->form = kSampledWalk;
+    p->clusters = 1;
+    p->max_visits = sampled_max_visits(wgs, V);
+    const long long n = pieces(part), masses = (long long)rows * n * 8;
+    if (T > p->max_visits && n <= kSampledMaxPieces) {
+      // two workgroups a compute unit, as the registers allow; the pieces' slots, then the rows' masses
+      long long clusters = kSampledEitherWgs * (long long)cus / (B * n);
+      const long long held = (room - masses - 256) / (B * n * kSampledManySlotBytes);
+      if (clusters > held) clusters = held;
+      if (clusters > T) clusters = T;
+      if (clusters > 1) {
+        p->form = kSampledEither;
+        p->clusters = (int)clusters;
+        p->mass_off = p->slot_off + align_up((size_t)(clusters * B * n * kSampledManySlotBytes), 256);
+        const long long small = pieces(kSampledParts[0]);
+        if (small <= kSampledMaxPieces && B * small <= cus) part = kSampledParts[0];
+        p->walk_chunks = (int)pieces(part);
+      }
+    }
+  }
   auto fits = [&] {
     const long long n = pieces(part * sub);
-    return n <= kSampledMaxPieces && (n == 1 || B * n * kSampledWalkSlotBytes <= (long long)(p->flag_off - p->slot_off));
+    return n <= kSampledMaxPieces && (n == 1 || B * n * kSampledManySlotBytes <= room);
   };
-  if (walk) {
+  if (p->form == kSampledWalk) {
     // the smallest part of which the batch's pieces take a compute unit each, so that all of them run at once on
     // as many units as there are; the largest, in rounds of sequences, for larger batches
     for (long long size : kSampledParts) {
@@ -587,10 +623,9 @@ dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPl
       for (sub = 2; !fits();) ++sub;
     }
   }
-  const long long chunks = pieces(part * sub);
+  const long long chunks = pieces(p->form == kSampledEither ? kSampledRowPart : part * sub);
   size_t stride = 16;
   while (stride > 4 && base + rows * stride > kMaxCounters) stride >>= 1;
-  p->walk = walk ? 1 : 0;
   p->part = (int)part;
   p->sub_pieces = (int)sub;
   p->chunks = (int)chunks;
@@ -661,7 +696,10 @@ dreams_status_t dreams_tree_accept_sampled(int32_t batch, int32_t num_nodes, int
   a.T = num_nodes;
   a.V = vocab;
   a.chunks = p.chunks;
-  a.walk = p.walk;
+  a.form = p.form;
+  a.clusters = p.clusters;
+  a.walk_chunks = p.walk_chunks;
+  a.max_visits = p.max_visits;
   a.part = p.part;
   a.sub_pieces = p.sub_pieces;
   a.vec4 = (vocab % 4 == 0) && aligned(target_logits, 16) && aligned(draft_logits, 16);

@@ -197,7 +197,10 @@ hipError_t launch_tree_accept(const AcceptArgs& a, hipStream_t stream);
 // Every vocabulary row is cut into pieces.  Row form: a workgroup per piece of every row, in row order (pieces of
 // 4096 entries).  Walk form: a workgroup per piece of every sequence, which takes only the rows that the
 // sequence's walk visits, one after the other: pieces of one part (2048 to 10240 entries, whose probabilities
-// stay in registers) or, for vocabularies that this does not hold, of several parts of 8192.
+// stay in registers) or, for vocabularies that this does not hold, of several parts of 8192.  Either form: the
+// workgroups of a walk (pieces of 2048 or 4096 entries), then those of `clusters` clusters a sequence, which take its
+// rows in turn (pieces of 4096); by the length of the tree's paths, one or the other leaves at once.
+enum SampledForm { kSampledRows, kSampledWalk, kSampledEither };
 constexpr int kSampledRowPart = 4096;
 constexpr int kSampledParts[] = {2048, 4096, 8192, 10240};
 constexpr int kSampledStreamPart = 8192;
@@ -205,7 +208,7 @@ constexpr int kSampledMaxPieces = 64;       // pieces per row, at most: one wave
 constexpr int kSampledRowCounter = 2;       // a row's words: its child word (64 bits), then its counter
 constexpr uint32_t kClusterLeft = 1u << 16; // a cluster's counter: pieces entered below, pieces left from here up
 constexpr int kSampledRowSlotBytes = 32;    // a piece's exchange slots
-constexpr int kSampledWalkSlotBytes = 64;
+constexpr int kSampledManySlotBytes = 64;   // ... of a cluster that takes many rows
 
 struct SampledArgs {
   const float* target_logits;  // [B, T, V]
@@ -216,18 +219,22 @@ struct SampledArgs {
   int32_t* accept_len;         // [B]
   int32_t* accept_path;        // [B, T]
   int32_t* next_token;         // [B]
-  uint32_t* seq_ctr;           // [B] row form: rows finished; walk form: pieces entered and left
-  uint32_t* row_ctr;           // [B * T] row form: the words of every row, row_stride words apart: as a child, its
-                               // residual mass, decision and arrivals; as a row, pieces entered and left
+  uint32_t* seq_ctr;           // [B] by rows: clusters finished; walked: pieces entered and left
+  uint32_t* row_ctr;           // [B * T] by rows: the words of every row, row_stride words apart: as a child, its
+                               // residual mass, decision and arrivals; as a cluster's first row, pieces entered and
+                               // left
   int row_stride;
   double* mass;                // [B, T, chunks] row form: residual mass of each piece after rejecting child c
-  uint64_t* slots;             // [B (row form: B * T), chunks] the pieces' exchange slots
+  uint64_t* slots;             // [B * clusters, chunks] the pieces' exchange slots
   int32_t* kept;               // [B, T] child c's decision (row form)
   int32_t* final_token;        // [B, T] the token emitted if the walk ends at node i (row form)
   double inv_tau;              // 1 / temperature (may be +inf)
   int B, T, V, chunks;
-  int walk;                    // 1: the walk form
-  int part;                    // entries of a part
+  int form;                    // SampledForm
+  int clusters;                // of a sequence: T (row form), 1 (walk form) or between
+  int walk_chunks;             // either form: pieces of a row that is walked (else 0)
+  int max_visits;              // either form: nodes of the longest path that is still walked
+  int part;                    // entries of a part (either form: of a row that is walked)
   int sub_pieces;              // parts per piece (1: held in registers)
   int vec4;                    // both logits tensors 16-byte aligned and V % 4 == 0
   uint32_t* err;               // the workspace's failure flags

@@ -19,7 +19,7 @@
 //   (3) draw the token emitted if the walk ends at the node: the prefix of the piece masses (of the last child
 //       that moved the state, or of p) names the piece where the cumulative mass first exceeds u0 * total, and
 //       that piece finds the token by a block scan.
-// Two forms place this work.  Only the rows that the walk visits matter -- the root's and each kept child's --
+// Three forms place this work.  Only the rows that the walk visits matter -- the root's and each kept child's --
 // but which they are is known only as the walk goes:
 //   * walk form: a workgroup per piece of every sequence.  The sequence's pieces take the walk's rows one after
 //     the other, deciding alike; only those rows are read.  Time grows with the walk's length.
@@ -30,10 +30,13 @@
 //     walks the decisions by ballots.  Time grows with the number of rows, not with the walk's length.  60 nodes x
 //     32000 entries: 24.5 us (28.6 with the statistics merged through a counter and a second round of loads, and
 //     butterfly reductions through LDS); a chain of exchanges as long as the widest node's children.
+//   * either form: a sequence whose tree has no path of more than `max_visits` nodes is walked; any other takes its
+//     rows all the same, in turn by a few clusters, so that a long path that is kept costs no more than that.  Both
+//     kinds of workgroup are launched and read the paths off the parents, and one kind leaves at once.
 // Probabilities are fp64, so that the integer outcome is decided in the precision of the definition; exp is
 // Tang's table-driven method.
 //
-// Exchange.  The pieces of a row (row form) or sequence (walk form) are a cluster.  In step s = 1, 2, ... (a row's
+// Exchange.  The pieces of a row (row form), of several rows (either form) or of a sequence (walk form) are a cluster.  In step s = 1, 2, ... (a row's
 // statistics, and in the walk form every child tested) every piece stores its few words, each 48 bits of data beside the step's number, to its own slot, and one wave
 // polls all slots of the cluster, lane k the slot of piece k, until every word carries the step's number: one
 // store and one load of latency, with no counter in between.  Slots alternate between two places: a piece
@@ -214,17 +217,19 @@ __device__ __forceinline__ void list_children(int n, int T, const int* par, Shar
   if (lane == 0) sh.nsib = __builtin_popcountll(b0) + __builtin_popcountll(b1);
 }
 
-// Piece j of a cluster, one row at a time.  WALK: the cluster takes many rows.  HOLD: a one-part piece (NT * E entries) keeps p and q in registers;
-// else the piece's parts are streamed from memory in every pass over them.
-template <bool VEC, bool WALK, bool HOLD, int NT, int E>
+// Piece j of a cluster, one row at a time.  WALK: its rows are those of a walk.  MANY: it takes more than one row.
+// HOLD: a one-part piece (NT * E entries) keeps p and q in registers; else the piece's parts are streamed from memory
+// in every pass over them.
+template <bool VEC, bool WALK, bool MANY, bool HOLD, int NT, int E>
 struct Piece {
   static constexpr int PART = NT * E, NW = NT / 64;
-  // 64-bit words of a piece's slots, four each; the walk form's steps alternate between two
-  static constexpr int WORDS = 4, SLOTS = WALK ? 2 * WORDS : WORDS;
-  static_assert(SLOTS * 8 == (WALK ? kSampledWalkSlotBytes : kSampledRowSlotBytes), "slot layout");
+  // 64-bit words of a piece's slots, four each; the steps of a cluster of many rows alternate between two
+  static constexpr int WORDS = 4, SLOTS = MANY ? 2 * WORDS : WORDS;
+  static_assert(MANY || !WALK, "a walk takes many rows");
+  static_assert(SLOTS * 8 == (MANY ? kSampledManySlotBytes : kSampledRowSlotBytes), "slot layout");
   const SampledArgs& a;
   Shared& sh;
-  const int b, j;
+  const int b, j, chunks;         // the sequence; this piece and the number of them
   uint32_t* const counter;        // the cluster's counter: pieces entered and (from kClusterLeft up) pieces left
   uint64_t* const slots;          // [chunks][SLOTS]
   uint32_t step = 0;
@@ -237,20 +242,20 @@ struct Piece {
   double mass = 0.0;              // wave 0, lane k: piece k's part of the state's mass ...
   int src = -1;                   // ... unless it is that of child src (row form: stored by the pieces)
 
-  __device__ __forceinline__ Piece(const SampledArgs& args, Shared& s, int seq, int piece, uint32_t* ctr,
-                                   size_t cluster)
-      : a(args), sh(s), b(seq), j(piece), counter(ctr), slots(args.slots + cluster * args.chunks * SLOTS) {}
+  // at: index of the cluster's first piece among all that have slots
+  __device__ __forceinline__ Piece(const SampledArgs& args, Shared& s, int seq, int piece, int pieces, uint32_t* ctr,
+                                   size_t at)
+      : a(args), sh(s), b(seq), j(piece), chunks(pieces), counter(ctr), slots(args.slots + at * SLOTS) {}
 
   __device__ __forceinline__ bool wave0() const { return threadIdx.x < 64; }
 
-  // Clears this piece's slots and counts it in.
-  __device__ __forceinline__ void enter() {
-    if (wave0()) {
-      const int l = threadIdx.x;
-      if (l < SLOTS && a.chunks > 1) store_u64(slots + j * SLOTS + l, 0);
-      wait_vector_memory();
-      if (l == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+  // Clears this piece's slots; count_in() counts it in, once they are cleared, after its first statistics.
+  __device__ __forceinline__ void clear_slots() {
+    if (threadIdx.x < SLOTS && chunks > 1) store_u64(slots + j * SLOTS + threadIdx.x, 0);
+  }
+  __device__ __forceinline__ void count_in() {
+    wait_vector_memory();
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   static __device__ __forceinline__ void store_u64(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -278,7 +283,7 @@ struct Piece {
                                            uint32_t (&all16)[N]) {
     const int l = threadIdx.x;
     ++step;
-    if (a.chunks == 1) {
+    if (chunks == 1) {
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         all[k] = (uint32_t)__builtin_amdgcn_readlane((int)mine, k);
@@ -286,16 +291,16 @@ struct Piece {
       }
       return bit;
     }
-    const int at = WALK && step % 2 == 0 ? WORDS : 0;
+    const int at = MANY && step % 2 == 0 ? WORDS : 0;
     if (l < N)
       store_u64(slots + j * SLOTS + at + l, ((uint64_t)mine << 32) | ((uint64_t)mine16 << 16) | step |
                                                 (l == N - 1 && bit ? kKeptBit : 0u));
     if (step == 1)   // every piece has cleared its slots
       wait_until([&] {
         return (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kClusterLeft - 1)) ==
-               (uint32_t)a.chunks;
+               (uint32_t)chunks;
       });
-    const uint64_t* from = slots + min(l, a.chunks - 1) * SLOTS + at;
+    const uint64_t* from = slots + min(l, chunks - 1) * SLOTS + at;
     bool kept = false;
     wait_until([&] {
       uint64_t w[N];
@@ -420,6 +425,7 @@ struct Piece {
       sh.wave_st[wave] = st;
       sh.wave_sd[wave] = sd;
     }
+    if (wave0() && step == 0) count_in();
     __syncthreads();
     if (wave0()) {
       float m1 = tid < NW ? sh.wave_mt[tid % NW] : -INFINITY, m2 = tid < NW ? sh.wave_md[tid % NW] : -INFINITY;
@@ -433,7 +439,7 @@ struct Piece {
       const uint32_t mine16 = ((tid < 2 ? low(s2) : high(s2)) >> (tid & 1 ? 16 : 0)) & 0xffffu;
       uint32_t w[4], h[4];
       exchange<4>(mine, mine16, false, w, h);
-      const bool in = tid < a.chunks;
+      const bool in = tid < chunks;
       m1 = in ? __builtin_bit_cast(float, w[0]) : -INFINITY;
       m2 = in ? __builtin_bit_cast(float, w[1]) : -INFINITY;
       s1 = in ? from_words(w[2], w[3]) : 0.0;
@@ -505,14 +511,14 @@ struct Piece {
       z = wave_sum(tid < NW ? sh.wave_z[tid % NW] : 0.0);
       const bool keep = sh.keep_here != 0;
       bool kept;
-      if (WALK || a.chunks == 1) {
+      if (WALK || chunks == 1) {
         uint32_t w[2], h[2];
         kept = exchange<2>(tid == 0 ? low(z) : high(z), 0, keep, w, h);
-        kept = __ballot(kept && tid < a.chunks) != 0;
-        part = tid < a.chunks ? from_words(w[0], w[1]) : 0.0;
+        kept = __ballot(kept && tid < chunks) != 0;
+        part = tid < chunks ? from_words(w[0], w[1]) : 0.0;
         z = wave_sum(part);
       } else {
-        if (tid == 0) store_d(a.mass + (rb + c) * a.chunks + j, z);
+        if (tid == 0) store_d(a.mass + (rb + c) * chunks + j, z);
         if (last) wait_vector_memory();   // (the piece's masses are stored before its last arrival)
         // A piece's mass is at most 1 (up to rounding), a row's below 2, so that the decision's bit is free.  After
         // its wait gave up a piece's mass is meaningless and counts as 0; the others have read the statistics of
@@ -524,7 +530,7 @@ struct Piece {
         uint64_t v = 0;
         wait_until([&] {
           v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          return (int)(v >> kArrivalShift) == a.chunks;
+          return (int)(v >> kArrivalShift) == chunks;
         });
         kept = (v & kKeptWordBit) != 0;
         z = (double)(v & (kKeptWordBit - 1)) * kFixUnit;
@@ -551,8 +557,8 @@ struct Piece {
   __device__ __forceinline__ int draw() {
     const int tid = threadIdx.x, V = a.V, wave = tid >> 6;
     if (wave0()) {
-      if (!WALK && src >= 0 && a.chunks > 1)
-        mass = tid < a.chunks ? load_d(a.mass + ((size_t)b * a.T + src) * a.chunks + tid) : 0.0;
+      if (!WALK && src >= 0 && chunks > 1)
+        mass = tid < chunks ? load_d(a.mass + ((size_t)b * a.T + src) * chunks + tid) : 0.0;
       const double inc = wave_scan(mass);
       const double thr = (double)a.uniforms[(size_t)b * a.T] * lane_of(inc, 63);
       const uint64_t over = __ballot(inc > thr), some = __ballot(mass > 0.0);
@@ -635,7 +641,7 @@ struct Piece {
   // (thread 0, once this piece's stores are done) counts this piece out; true in the cluster's last one
   __device__ __forceinline__ bool leave() {
     return __hip_atomic_fetch_add(counter, kClusterLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kClusterLeft ==
-           (uint32_t)(a.chunks - 1);
+           (uint32_t)(chunks - 1);
   }
 };
 
@@ -681,6 +687,33 @@ __device__ void walk_decisions(const SampledArgs& a, int b, Shared& sh) {
   }
 }
 
+// Row n (loaded, its children listed): its children's decisions, and the token emitted if the walk ends there.
+template <typename P>
+__device__ __forceinline__ void take_row(const SampledArgs& a, Shared& sh, P& pc, int b, int n) {
+  pc.statistics();
+  const int nsib = sh.nsib;
+  for (int k = 0; k < nsib && !sh.gave_up; ++k) pc.test_child(sh.sib[k], k == nsib - 1);
+  const int pick = pc.draw();
+  if (pick >= 0 && threadIdx.x == 0) store_coherent(a.final_token + (size_t)b * a.T + n, pick);
+}
+// The piece has taken its cluster's rows.
+template <typename P>
+__device__ __forceinline__ void rows_done(const SampledArgs& a, Shared& sh, P& pc, int b) {
+  // Every piece counts itself out once its decisions and tokens are stored; the cluster's last piece counts it as
+  // done, and the sequence's last cluster runs the walk.
+  wait_vector_memory();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    sh.flag = pc.leave() && __hip_atomic_fetch_add(a.seq_ctr + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                                (uint32_t)(a.clusters - 1);
+  __syncthreads();
+  if (sh.flag) walk_decisions(a, b, sh);
+}
+
+__device__ __forceinline__ uint32_t* row_counter(const SampledArgs& a, int b, int n) {
+  return a.row_ctr + ((size_t)b * a.T + n) * a.row_stride + kSampledRowCounter;
+}
+
 // Workgroup (b, n, j): piece j of row n.
 template <bool VEC, int NT, int E>
 __global__ __launch_bounds__(NT) void tree_accept_sampled_rows_kernel(SampledArgs a) {
@@ -688,48 +721,23 @@ __global__ __launch_bounds__(NT) void tree_accept_sampled_rows_kernel(SampledArg
   const int tid = threadIdx.x, T = a.T;
   const int j = (int)(blockIdx.x % (unsigned)a.chunks), row = (int)(blockIdx.x / (unsigned)a.chunks);
   const int b = row / T, n = row - b * T;
-  const size_t rb = (size_t)b * T;
-  Piece<VEC, false, true, NT, E> pc(a, sh, b, j, a.row_ctr + (size_t)row * a.row_stride + kSampledRowCounter, row);
-  pc.enter();
+  Piece<VEC, false, false, true, NT, E> pc(a, sh, b, j, a.chunks, row_counter(a, b, n), (size_t)row * a.chunks);
+  pc.clear_slots();
   pc.load(n);
   if (tid < 256) sh.tab[tid] = exp2((double)tid * (1.0 / 256.0));
-  if (tid < 64) list_children(n, T, a.parent + rb, sh);
+  if (tid < 64) list_children(n, T, a.parent + (size_t)b * T, sh);
   if (tid == 0) sh.gave_up = sh.keep_here = 0;
   __syncthreads();
-  pc.statistics();
-  const int nsib = sh.nsib;
-  for (int k = 0; k < nsib && !sh.gave_up; ++k) pc.test_child(sh.sib[k], k == nsib - 1);
-  const int pick = pc.draw();
-  if (pick >= 0 && tid == 0) store_coherent(a.final_token + row, pick);
-  // Every piece counts itself out once its decisions and token are stored; the row's last piece counts the row
-  // as done, and the sequence's last row runs the walk.
-  wait_vector_memory();
-  __syncthreads();
-  if (tid == 0)
-    sh.flag = pc.leave() && __hip_atomic_fetch_add(a.seq_ctr + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                                (uint32_t)(T - 1);
-  __syncthreads();
-  if (sh.flag) walk_decisions(a, b, sh);
+  take_row(a, sh, pc, b, n);
+  rows_done(a, sh, pc, b);
 }
 
 // --------------------------------------------------------------------------------------------- walk form
-// Workgroup (b, j): piece j of every row that sequence b's walk visits, from the root down.
-template <bool VEC, bool HOLD, int NT, int E>
-__global__ __launch_bounds__(NT) void tree_accept_sampled_walk_kernel(SampledArgs a) {
-  __shared__ Shared sh;
+// Piece j of the cluster that walks sequence b, its first row loaded: every row that the walk visits, from the root.
+template <typename P>
+__device__ __forceinline__ void walk_rows(const SampledArgs& a, Shared& sh, P& pc, int b, int j) {
   const int tid = threadIdx.x, T = a.T;
-  const int b = (int)(blockIdx.x / (unsigned)a.chunks), j = (int)(blockIdx.x % (unsigned)a.chunks);
   const size_t rb = (size_t)b * T;
-  Piece<VEC, true, HOLD, NT, E> pc(a, sh, b, j, a.seq_ctr + b, b);
-  pc.enter();
-  pc.load(0);
-  if (tid < 256) sh.tab[tid] = exp2((double)tid * (1.0 / 256.0));
-  if (tid < T) sh.par[tid] = a.parent[rb + tid];
-  if (tid == 0) {
-    sh.gave_up = sh.keep_here = 0;
-    sh.path[0] = 0;
-  }
-  __syncthreads();
   int depth = 0;
   for (int node = 0;;) {
     if (tid < 64) list_children(node, T, sh.par, sh);
@@ -758,18 +766,100 @@ __global__ __launch_bounds__(NT) void tree_accept_sampled_walk_kernel(SampledArg
   if (tid == 0 && pc.leave()) reset_counter(a.seq_ctr + b);
 }
 
+__device__ __forceinline__ void start_walk(const SampledArgs& a, Shared& sh, int b) {
+  const int tid = threadIdx.x;
+  if (tid < 256) sh.tab[tid] = exp2((double)tid * (1.0 / 256.0));
+  if (tid < a.T) sh.par[tid] = a.parent[(size_t)b * a.T + tid];
+  if (tid == 0) {
+    sh.gave_up = sh.keep_here = 0;
+    sh.path[0] = 0;
+  }
+  __syncthreads();
+}
+
+// Workgroup (b, j): piece j of sequence b's walk.
+template <bool VEC, bool HOLD, int NT, int E>
+__global__ __launch_bounds__(NT) void tree_accept_sampled_walk_kernel(SampledArgs a) {
+  __shared__ Shared sh;
+  const int b = (int)(blockIdx.x / (unsigned)a.chunks), j = (int)(blockIdx.x % (unsigned)a.chunks);
+  Piece<VEC, true, true, HOLD, NT, E> pc(a, sh, b, j, a.chunks, a.seq_ctr + b, (size_t)b * a.chunks);
+  pc.clear_slots();
+  pc.load(0);
+  start_walk(a, sh, b);
+  walk_rows(a, sh, pc, b, j);
+}
+
+// ------------------------------------------------------------------------------------------- either form
+// Whether some path from the root has more than `most` nodes, breadth-first over ballots (lane l holds nodes l and
+// l + 64); the same in every wave.
+__device__ __forceinline__ bool path_longer_than(const int* par, int T, int most) {
+  const int lane = threadIdx.x & 63;
+  const int p0 = lane < T ? par[lane] : -1, p1 = lane + 64 < T ? par[lane + 64] : -1;
+  const bool v0 = p0 >= 0 && p0 < lane, v1 = p1 >= 0 && p1 < lane + 64;
+  uint64_t s0 = 1, s1 = 0;   // the nodes at this depth
+  for (int nodes = 1; (s0 | s1) != 0; ++nodes) {
+    if (nodes > most) return true;
+    const bool n0 = v0 && (s0 >> p0 & 1) != 0;
+    const bool n1 = v1 && ((p1 < 64 ? s0 >> p1 : s1 >> (p1 - 64)) & 1) != 0;
+    s0 = __ballot(n0);
+    s1 = __ballot(n1);
+  }
+  return false;
+}
+
+// First a workgroup per piece of every sequence's walk (EW entries a thread), which leave where the tree has longer
+// paths; then workgroups (c, b, j), piece j (ER entries a thread) of sequence b's cluster c, which takes rows c,
+// c + clusters, ..., and leave where it has not.  A sequence's walk has the slots of its clusters.
+template <bool VEC, int NT, int EW, int ER>
+__global__ __launch_bounds__(NT, 4) void tree_accept_sampled_either_kernel(SampledArgs a) {
+  __shared__ Shared sh;
+  const int n = (int)blockIdx.x, walkers = a.B * a.walk_chunks;
+  if (n < walkers) {
+    const int b = n / a.walk_chunks, j = n - b * a.walk_chunks;
+    Piece<VEC, true, true, true, NT, EW> pc(a, sh, b, j, a.walk_chunks, a.seq_ctr + b,
+                                            (size_t)b * a.clusters * a.chunks);
+    pc.load(0);
+    start_walk(a, sh, b);
+    if (path_longer_than(sh.par, a.T, a.max_visits)) return;
+    pc.clear_slots();
+    walk_rows(a, sh, pc, b, j);
+    return;
+  }
+  const int r = (n - walkers) / a.chunks, j = n - walkers - r * a.chunks;
+  const int c = r / a.B, b = r - c * a.B;
+  Piece<VEC, false, true, true, NT, ER> pc(a, sh, b, j, a.chunks, row_counter(a, b, c),
+                                           ((size_t)b * a.clusters + c) * a.chunks);
+  start_walk(a, sh, b);
+  if (!path_longer_than(sh.par, a.T, a.max_visits)) return;
+  pc.clear_slots();
+  for (int row = c; row < a.T; row += a.clusters) {
+    pc.load(row);
+    if (threadIdx.x < 64) list_children(row, a.T, sh.par, sh);
+    take_row(a, sh, pc, b, row);
+    if (sh.gave_up) break;
+  }
+  rows_done(a, sh, pc, b);
+}
+
 }  // namespace
 
 hipError_t launch_tree_accept_sampled(const SampledArgs& a, hipStream_t stream) {
   if (a.chunks > kSampledMaxPieces) return hipErrorInvalidValue;
-  const long long grid = (long long)a.B * (a.walk ? 1 : a.T) * a.chunks;
+  const long long grid = (long long)a.B * ((long long)a.clusters * a.chunks + a.walk_chunks);
   auto go = [&](auto kern, int threads) {
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, stream, a);
     return hipGetLastError();
   };
-  if (!a.walk)
+  if (a.form == kSampledRows)
     return a.vec4 ? go(tree_accept_sampled_rows_kernel<true, 512, 8>, 512)
                   : go(tree_accept_sampled_rows_kernel<false, 512, 8>, 512);
+  if (a.form == kSampledEither) {
+    if (a.part == 4 * 512)
+      return a.vec4 ? go(tree_accept_sampled_either_kernel<true, 512, 4, 8>, 512)
+                    : go(tree_accept_sampled_either_kernel<false, 512, 4, 8>, 512);
+    return a.vec4 ? go(tree_accept_sampled_either_kernel<true, 512, 8, 8>, 512)
+                  : go(tree_accept_sampled_either_kernel<false, 512, 8, 8>, 512);
+  }
 #define DREAMS_WALK(HOLD, NT, E)                                                        \
   return a.vec4 ? go(tree_accept_sampled_walk_kernel<true, HOLD, NT, E>, NT)            \
                 : go(tree_accept_sampled_walk_kernel<false, HOLD, NT, E>, NT)

@@ -229,3 +229,60 @@ def test_walk_form(dev, B, T, V):
     for _ in range(2):
         run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "walk form %s" % ((B, T, V),), workspace=ws)
     assert not ws[:65536].any()
+
+
+@pytest.mark.parametrize("B,T,V,depths", [
+    (3, 60, 32000, (8, 9, 59)),        # 1440 row pieces: paths of 9 nodes are walked (2048 entries a piece), of 10 not
+    (3, 60, 32001, (9, 8, 3)),         # ... with scalar loads
+    (17, 60, 32000, (36, 37, 59)),     # walked in pieces of 4096 entries
+    (2, 65, 32000, (64, 20)),          # just past the row form; as many clusters as their slots have room
+    (9, 128, 1000, (7, 8, 40)),        # a row in one workgroup
+    (2, 24, 262144, (10, 11)),         # 64 pieces a row
+])
+def test_short_paths_walked_long_ones_by_rows(dev, B, T, V, depths):
+    """Sequences of one call whose trees have paths on either side of the length that is still walked; drafts that
+    follow the target and, in the last sequence, drafts that are all kept."""
+    rng = np.random.default_rng(B + T + V)
+    tl, dl, tok, _, uni = random_case(rng, B, T, V, 1, T)
+    deep = [depths[-1] if b == B - 1 else depths[b % len(depths)] for b in range(B)]
+    par = np.stack([W.random_tree(rng, T, d, 3 if d > 4 else 9) for d in deep])
+    dl[B - 1] = tl[B - 1]
+    for b in range(B):
+        for i in range(1, T):
+            tok[b, i] = int(np.argmax(dl[b, par[b, i]] - np.log(-np.log(rng.random(V)))))
+    ws = torch.zeros(dreams.tree_accept_sampled_workspace_size(B, T, V), dtype=torch.uint8, device=dev)
+    ws[65536:] = 0xA5
+    for _ in range(2):
+        ra = run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "either form %s" % ((B, T, V, depths),), workspace=ws)
+    assert deep[B - 1] < T - 1 or ra[B - 1] == T - 1
+    assert not ws[:65536].any()
+    dreams.workspace_status(ws)
+
+
+def test_a_long_path_costs_the_same_kept_or_not(dev):
+    """A chain takes its rows in parallel: kept throughout, it takes no more than twice what it takes where the first
+    draft is rejected (a walk of 60 rows, one after the other, took nine times as long)."""
+    B, T, V = 4, 60, 32000
+    g = torch.Generator(device=dev)
+    g.manual_seed(81)
+    tl = torch.randn((B, T, V), generator=g, device=dev) * 3
+    par = to_dev(np.tile(W.chain_tree(T), (B, 1)), dev)
+    tok = tl.argmax(dim=2).int().roll(1, dims=1).contiguous()       # each node's draft: its parent's best token
+    uni = torch.rand((B, T), generator=g, device=dev)
+    far = -tl                                                       # a draft that the target never follows
+    tok_far = far.argmax(dim=2).int().roll(1, dims=1).contiguous()
+    us = []
+    for dl, tk in ((far, tok_far), (tl, tok)):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        times = []
+        for _ in range(20):
+            a.record()
+            for _ in range(10):
+                out = dreams.tree_accept_sampled(tl, dl, tk, par, uni, 1.0)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 100.0)
+        us.append(float(np.median(times)))
+        assert torch.all(out[0] == (0 if dl is far else T - 1))
+    note("a chain of %d: first draft rejected %.1f us, all kept %.1f us" % (T, us[0], us[1]))
+    assert us[1] <= 2.0 * us[0]
