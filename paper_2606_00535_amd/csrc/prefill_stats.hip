@@ -6,11 +6,11 @@
 //     entropy[h,i] = -sum_{j <= i} A[h,i,j] log A[h,i,j],   A[h,i,j] = exp(scale * q_i . k_j - lse[h,i]).
 // No value product is needed, so this is half of a causal attention forward.
 //
-//   * prefill_stats_kernel: a workgroup of 8 waves owns 128 query rows of one query head; a wave owns 32 rows
-//     as two 16-row matrix-core B operands (its queries stay in registers).  The prompt's keys 0 .. the
-//     workgroup's last row stream through an LDS ring of 64-key stages (LDS-DMA copies, several stages ahead);
-//     four waves take each stage's first 32 keys, four its second 32 (their states meet in LDS at the end):
-//     S^T = K Q^T on v_mfma_f32_16x16x32_bf16 with the key rows as the A operand.
+//   * prefill_stats_kernel: a workgroup of 8 waves owns 128 or 256 query rows of one query head; a wave owns 32
+//     rows as two 16-row matrix-core B operands (its queries stay in registers).  The prompt's keys 0 .. the
+//     workgroup's last row stream through an LDS ring of 64-key stages (LDS-DMA copies, several stages ahead); of
+//     128 rows, four waves take each stage's first 32 keys, four its second 32 (their states meet in LDS at the
+//     end): S^T = K Q^T on v_mfma_f32_16x16x32_bf16 with the key rows as the A operand.
 //     Each lane keeps, for each of its 2 rows, an online (reference, sum, entropy term) over the keys its
 //     quad sees, in log2 units; the reference only moves when a score passes it by more than 2^8 (the sums
 //     stay finite and the statistics do not depend on it), and the four quads are merged at the end.  Only
@@ -19,7 +19,7 @@
 //     most keys start first; a single round's second half takes them in the opposite order.
 //     What bounds it is the vector ALU (77 % of its issue slots: per score an fma, an exp2 at a quarter rate,
 //     an add and an fma, beside a quarter of a matrix instruction), as long as every compute unit holds two
-//     workgroups to the end: 256-row workgroups left the longest alone with two waves a SIMD.  3136 rows x 32
+//     workgroups to the end: with few workgroups, 256-row ones leave the longest alone with two waves a SIMD.  3136 rows x 32
 //     heads x 128: 85 us as 256-row workgroups, 72 us as 128-row ones, 63 us with the masked blocks apart, the
 //     maxima as three-input chains and the reference test on unscaled products (kernel times).
 //   * prefill_entropy_mean_kernel: one workgroup, the fp64 mean of the prompt rows' entropies over every head
@@ -38,8 +38,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 8;
 constexpr int kRB = 2;                        // 16-row blocks per wave
 constexpr int kRowsPerWave = 16 * kRB;
-constexpr int kKeyGroups = 2;                 // halves of a stage, each taken by half of the waves
-constexpr int kRowsPerWg = kRowsPerWave * kWaves / kKeyGroups;
+constexpr int kRowsPerWgMax = kRowsPerWave * kWaves;   // over the key groups (see below)
 constexpr int kKeys = 64;                     // keys per ring stage
 constexpr int kStages = 4;                    // ring stages
 constexpr float kLazyLog2 = 8.0f;             // slack of the reference before it moves
@@ -119,9 +118,12 @@ __device__ __forceinline__ void rescale(float& m, float& l, float& e, float M) {
   m = M;
 }
 
-template <int D>
+// KG key groups: each takes its part of every stage, with kWaves / KG of the waves
+template <int D, int KG>
 __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillArgs a) {
   using L = KRows<D>;
+  constexpr int kRowsPerWg = kRowsPerWgMax / KG, kRowWaves = kWaves / KG, KPG = kKeys / KG;
+  static_assert(KG == 1 || KG == 2, "one or two 32-key halves of a stage per group");
   constexpr int DS = D / 32;
   constexpr int STAGE = kKeys * L::ROW;          // bytes of a stage
   constexpr int CPW = STAGE / 1024 / kWaves;     // wave-wide 1 KB copies per wave per stage
@@ -143,8 +145,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
   nb = nb < 0 ? 0 : (nb > a.N ? a.N : nb);
 
   const int r0 = blk * kRowsPerWg;                  // the workgroup's first row
-  constexpr int kRowWaves = kWaves / kKeyGroups;
-  const int kgrp = wave / kRowWaves;                // the wave's half of every stage
+  const int kgrp = wave / kRowWaves;                // the wave's part of every stage
   const int rw0 = r0 + (wave % kRowWaves) * kRowsPerWave;   // the wave's first row
   const size_t qrow0 = ((size_t)b * a.Hq + h) * a.N;
   const unsigned char* kbase = (const unsigned char*)a.k + ((size_t)b * a.Hkv + g) * a.S_cap * L::ROW;
@@ -198,15 +199,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
   const int ka_row = (col & 3) * 4 + (col >> 2);   // A row m holds key kb*16 + (m%4)*4 + m/4
   const int wlast = min(rw0 + kRowsPerWave, nb) - 1;   // the wave's last live row (< rw0: none)
 
-  // The wave's 32 keys of a stage (two 16-key blocks): lane (col, quad) gets keys kk0 + 16 kb + 4 t + quad
+  // 32 keys of a stage, its first or second half (two 16-key blocks): lane (col, quad) gets keys kk0 + 16 kb + 4 t + quad
   // (t = 0..3) of rows rw0 + 16 rb + col.
-  auto products = [&](f32x4 (&s)[kRB][2], const unsigned char* tile) {
+  auto products = [&](f32x4 (&s)[kRB][2], const unsigned char* tile, int half) {
     bf16x8 kf[2][DS];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int ds = 0; ds < DS; ++ds)
-        kf[kb][ds] = *(const bf16x8*)(tile + L::off((kgrp * 2 + kb) * 16 + ka_row, ds * 4 + quad));
+        kf[kb][ds] = *(const bf16x8*)(tile + L::off((half * 2 + kb) * 16 + ka_row, ds * 4 + quad));
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds)
 #pragma unroll
@@ -292,24 +293,29 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
   };
   // The wave's plain stages come first, then those it masks, then those that no live row of it sees; every wave
   // passes every stage's barrier, in whichever loop.
-  constexpr int KPG = kKeys / kKeyGroups;
   const int first = kgrp * KPG;   // the wave's first key of a stage
   const int lim = min(rw0, nb - 1) - (KPG - 1) - first;   // plain: st * kKeys <= lim
   const int plain = min(nst, lim >= 0 ? lim / kKeys + 1 : 0);
   int st = 0;
   for (; st < plain; ++st) {
     next_stage(st);
-    f32x4 s[kRB][2];
-    products(s, ring + (st % kStages) * STAGE);
-    plain_block(s);
+#pragma unroll
+    for (int half = 0; half < KPG / 32; ++half) {
+      f32x4 s[kRB][2];
+      products(s, ring + (st % kStages) * STAGE, kgrp + half);
+      plain_block(s);
+    }
   }
   for (; st < nst; ++st) {
     next_stage(st);
-    const int kk0 = st * kKeys + first;
-    if (kk0 > wlast) continue;   // (wave-uniform)
-    f32x4 s[kRB][2];
-    products(s, ring + (st % kStages) * STAGE);
-    edge_block(s, kk0);
+#pragma unroll
+    for (int half = 0; half < KPG / 32; ++half) {
+      const int kk0 = st * kKeys + first + half * 32;
+      if (kk0 > wlast) break;   // (wave-uniform)
+      f32x4 s[kRB][2];
+      products(s, ring + (st % kStages) * STAGE, kgrp + half);
+      edge_block(s, kk0);
+    }
   }
 
   wait_vm<0>();   // (a workgroup with no live row has not waited for its first copies)
@@ -325,7 +331,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
     l1 += l2;
     e1 += e2;
   };
-  barrier_lds();   // every wave is done with the ring
+  if (KG > 1) barrier_lds();   // every wave is done with the ring
   float* st_lds = (float*)ring;   // [3][kRowsPerWg]: the second key group's states
   const int rl0 = (wave % kRowWaves) * kRowsPerWave;
 #pragma unroll
@@ -340,12 +346,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
       st_lds[2 * kRowsPerWg + rl] = e[rb];
     }
   }
-  barrier_lds();
+  if (KG > 1) barrier_lds();
   if (kgrp != 0 || quad != 0) return;
 #pragma unroll
   for (int rb = 0; rb < kRB; ++rb) {
     const int rl = rl0 + rb * 16 + col;
-    merge(m[rb], l[rb], e[rb], st_lds[rl], st_lds[kRowsPerWg + rl], st_lds[2 * kRowsPerWg + rl]);
+    if (KG > 1) merge(m[rb], l[rb], e[rb], st_lds[rl], st_lds[kRowsPerWg + rl], st_lds[2 * kRowsPerWg + rl]);
     const int row = r0 + rl;
     if (row < a.N) {
       const bool live = row < nb && l[rb] > 0.f;
@@ -403,25 +409,40 @@ __global__ __launch_bounds__(1024) void prefill_entropy_mean_kernel(int B, int H
 
 }  // namespace
 
-template <int D>
-hipError_t launch_stats(const PrefillArgs& a, unsigned grid, hipStream_t stream) {
+template <int D, int KG>
+hipError_t launch_stats(const PrefillArgs& a, hipStream_t stream) {
   constexpr size_t lds = (size_t)kStages * kKeys * D * 2;
+  constexpr int rows = kRowsPerWgMax / KG;
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute((const void*)prefill_stats_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void*)prefill_stats_kernel<D, KG>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL(prefill_stats_kernel<D>, dim3(grid), dim3(64 * kWaves), lds, stream, a);
+  const long long grid = (long long)a.B * a.Hq * ((a.N + rows - 1) / rows);
+  hipLaunchKernelGGL((prefill_stats_kernel<D, KG>), dim3((unsigned)grid), dim3(64 * kWaves), lds, stream, a);
   return hipGetLastError();
 }
 
+// 256 rows a workgroup where that leaves four workgroups a compute unit (two, of one block each) and pads the rows by
+// no more than a tenth beyond 128-row blocks: the two key groups' uneven ends and their merge cost more there than the
+// shorter workgroups gain.  128 and 256 rows (us, head_dim 128): 16 x 40 heads x 500 rows 61, 52; x 256 27.3, 24.6;
+// 8 x 40 x 1024 77, 70; 4 x 32 x 2000 105, 88; 32 x 32 x 200 35, 28; but 32 x 3136 61, 67; 2 x 32 x 3136 107, 110;
+// 16 x 40 x 384 41, 44.  A prompt of at most 64 rows is one stage: 6.5, 6.0.
+template <int D>
+hipError_t launch_stats_rows(const PrefillArgs& a, hipStream_t stream) {
+  const long long half = (a.N + kRowsPerWgMax / 2 - 1) / (kRowsPerWgMax / 2), whole = (half + 1) / 2;
+  const long long grid = (long long)a.B * a.Hq * whole;
+  if (a.N <= kKeys || (20 * whole <= 11 * half && grid >= (whole == 1 ? 2LL : 4LL) * a.cus))
+    return launch_stats<D, 1>(a, stream);
+  return launch_stats<D, 2>(a, stream);
+}
+
 hipError_t launch_prefill_stats(const PrefillArgs& a, hipStream_t stream) {
-  const long long grid = (long long)a.B * a.Hq * ((a.N + kRowsPerWg - 1) / kRowsPerWg);
-  if (grid <= 0) return hipSuccess;
-  if (a.D == 128) return launch_stats<128>(a, (unsigned)grid, stream);
-  if (a.D == 64) return launch_stats<64>(a, (unsigned)grid, stream);
+  if (a.B * (long long)a.Hq == 0) return hipSuccess;
+  if (a.D == 128) return launch_stats_rows<128>(a, stream);
+  if (a.D == 64) return launch_stats_rows<64>(a, stream);
   return hipErrorInvalidValue;
 }
 

@@ -116,6 +116,22 @@ def test_prefill_edges_and_pieces(dev, case):
         assert not ws[:65536].cpu().numpy().any()
 
 
+WIDE = [  # enough workgroups for 256-row blocks, and prompts of one stage; ends of rows, waves and stages
+    (16, 32, 8, 64, (256, 225, 129), 3, 100),
+    (19, 28, 4, 128, (193, 255, 2, 128), 0, 120),
+    (6, 30, 30, 64, (1290, 1023, 1281), 7, 90),
+    (3, 4, 2, 128, (64, 33, 1), 0, 32),
+    (2, 3, 3, 64, (63, 32), 0, 30),
+]
+
+
+@pytest.mark.parametrize("case", WIDE, ids=["%dx%d_%d" % (c[0], c[1], max(c[4])) for c in WIDE])
+def test_prefill_wide_row_blocks(dev, case):
+    B, Hq, Hkv, D, lens, vb, vc = case
+    p = W.make_prompt(B, Hq, Hkv, D, tuple(lens[b % len(lens)] for b in range(B)), vb, vc, seed=67)
+    check(p, dev, "prefill wide %s" % (case,))
+
+
 def test_prefill_empty_prompt(dev):
     # a sequence with no prompt: every row -inf / 0, importance 0, and it does not count in AE
     p = W.make_prompt(2, 4, 4, 128, (0, 90), 0, 80, num_rows=96, seed=62)
