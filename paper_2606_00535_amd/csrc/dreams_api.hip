@@ -828,13 +828,21 @@ static_assert(kVisualMaxTokens == DREAMS_VISUAL_MAX_TOKENS, "top-r capacity");
 size_t visual_workspace_bytes(int batch, int num_kv_heads, int vis_count) {
   return kCounterBytes + (size_t)batch * num_kv_heads * vis_count * sizeof(float);
 }
-// Pieces that a prompt's rows are cut into (a workgroup each per sequence, KV head and 256 tokens): as many as make
-// about three workgroups per compute unit, at most 16.  A call whose workspace has room for fewer gets those.
-constexpr int kVisualTargetWgs = 768, kVisualMaxPieces = 16, kVisualPieceStages = 4;
-int visual_pieces(int batch, int num_kv_heads, int vis_count) {
-  const long long wgs = (long long)batch * num_kv_heads * ((vis_count + 255) / 256);
-  const long long n = wgs > 0 ? (kVisualTargetWgs + wgs - 1) / wgs : 1;
-  return (int)(n < kVisualMaxPieces ? n : kVisualMaxPieces);
+// Pieces that a prompt's rows are cut into (a workgroup each per sequence, KV head and 256 tokens), at most 16.  A call
+// whose workspace has room for fewer gets those.  Up to 300 workgroups: as many pieces of at least 4 stages (64 rows of
+// a head) as make about 600 workgroups, two a compute unit and a few (us, one KV head to a query head unless stated:
+// 32 on 8 heads x 2000 rows, 64 workgroups, 4, 8 and 12 pieces 53, 33.5, 37; 8 x 3136 rows, 96: 3, 5, 8: 32, 24, 27;
+// 16 x 3136, 192: 2, 3, 4: 44, 39, 39; 2 x 32 x 1200, 256: 1, 2, 3: 35, 26, 35).  From there to 768, two, where each
+// gets 12 stages: long rows gain by the even ends (32 x 3136, 384 workgroups: 78 in one, 62 in two), short ones only
+// pay the second start and sum (8 x 32 x 600, 512: 31 and 36; 6 x 32 x 600, 384: 28.5 and 31.6).
+constexpr int kVisualTargetWgs = 600, kVisualFewWgs = 300, kVisualMostWgs = 768, kVisualMaxPieces = 16;
+constexpr int kVisualStages = 4, kVisualStagesTwo = 12;
+long long visual_workgroups(int batch, int num_kv_heads, int vis_count) {
+  return (long long)batch * num_kv_heads * ((vis_count + 255) / 256);
+}
+int visual_pieces(long long wgs) {
+  if (wgs > kVisualFewWgs || wgs < 1) return wgs > kVisualFewWgs && wgs < kVisualMostWgs ? 2 : 1;
+  return (int)(kVisualTargetWgs / wgs < kVisualMaxPieces ? kVisualTargetWgs / wgs : kVisualMaxPieces);
 }
 int visual_counter_stride(int batch, int vis_count) {   // 0: the counters do not fit
   const long long n = (long long)batch * ((vis_count + 255) / 256);
@@ -970,7 +978,7 @@ dreams_status_t dreams_prefill_visual_importance_workspace_size(int32_t batch, i
                                                                 size_t* bytes) {
   dreams_status_t st = dreams_visual_importance_workspace_size(batch, num_kv_heads, vis_count, bytes);
   if (st != DREAMS_OK) return st;
-  *bytes = kCounterBytes + (*bytes - kCounterBytes) * visual_pieces(batch, num_kv_heads, vis_count);
+  *bytes = kCounterBytes + (*bytes - kCounterBytes) * visual_pieces(visual_workgroups(batch, num_kv_heads, vis_count));
   return ok();
 }
 
@@ -1010,10 +1018,10 @@ dreams_status_t dreams_prefill_visual_importance(const dreams_prefill_desc_t* de
   a.counters = (uint32_t*)workspace;
   a.counter_stride = stride;
   a.partial = (float*)((char*)workspace + kCounterBytes);
-  a.pieces = visual_pieces(desc->batch, desc->num_kv_heads, vis_count);
-  // (no piece of the longest block under kVisualPieceStages stages of 64 rows)
-  const long long by_rows =
-      (long long)(desc->num_q_heads / desc->num_kv_heads) * ((desc->num_rows + 63) / 64) / kVisualPieceStages;
+  const long long wgs = visual_workgroups(desc->batch, desc->num_kv_heads, vis_count);
+  a.pieces = visual_pieces(wgs);
+  const long long by_rows = (long long)(desc->num_q_heads / desc->num_kv_heads) * ((desc->num_rows + 63) / 64) /
+                            (wgs > kVisualFewWgs ? kVisualStagesTwo : kVisualStages);
   if (a.pieces > by_rows) a.pieces = by_rows > 1 ? (int)by_rows : 1;
   const size_t held = (workspace_bytes - kCounterBytes) / (need - kCounterBytes);
   if ((size_t)a.pieces > held) a.pieces = (int)held;

@@ -273,8 +273,9 @@ __global__ __launch_bounds__(64 * pf::kWaves, 2) void visual_importance_prefill_
   // rows that can see the block's tokens: i >= its first token's slot, in 64-row stages, head after head
   const int istart = min(L, max(0, a.vis_begin + blk * kImpKeys) & ~15);
   const int nsh = (L - istart + pf::kRows - 1) / pf::kRows;   // stages per head
-  const int t0 = (int)((long long)a.G * nsh * piece / P);   // this piece's stages [t0, t1)
-  const int t1 = (int)((long long)a.G * nsh * (piece + 1) / P);
+  // this piece's stages [t0, t1) (one piece: without the 64-bit divisions)
+  const int t0 = P > 1 ? (int)((long long)a.G * nsh * piece / P) : 0;
+  const int t1 = P > 1 ? (int)((long long)a.G * nsh * (piece + 1) / P) : a.G * nsh;
   const size_t row0 = ((size_t)b * a.Hq + (size_t)g * a.G) * T;   // the KV head's first query row
   const unsigned char* qbase = (const unsigned char*)a.q + row0 * L_::ROW;
   const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(pf::lds_addr(ring));

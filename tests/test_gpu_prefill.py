@@ -132,6 +132,38 @@ def test_prefill_wide_row_blocks(dev, case):
     check(p, dev, "prefill wide %s" % (case,))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,vis,pieces", [
+    (8, 32, 32, 600, 400, 1),       # 512 workgroups, 10 stages: in two they took 36 us, in one 31
+    (3, 104, 104, 700, 200, 1),     # 312, 11 stages
+    (3, 104, 104, 1600, 200, 2),    # 312, 25 stages
+    (19, 64, 16, 390, 200, 2),      # 304, four heads' 28 stages
+    (2, 32, 32, 1100, 1000, 2),     # 256
+    (3, 64, 64, 400, 250, 1),       # 192, 7 stages: not two pieces of four
+    (3, 64, 64, 520, 250, 2),       # ... 9
+    (1, 8, 8, 3000, 1500, 11),      # 48: 600 / 48 = 12, of 47 stages
+])
+def test_prefill_importance_pieces(dev, B, Hq, Hkv, N, vis, pieces):
+    """The sums of a call equal those with a workspace of exactly so many pieces bit for bit."""
+    g = torch.Generator(device=dev)
+    g.manual_seed(68)
+    q = torch.randn((B, Hq, N, 64), generator=g, device=dev).to(torch.bfloat16)
+    k = torch.randn((B, Hkv, (N + 63) // 64 * 64, 64), generator=g, device=dev).to(torch.bfloat16)
+    lens = torch.full((B,), N, dtype=torch.int32, device=dev)
+    lse, _ = dreams.prefill_attn_stats(q, k, lens, with_entropy=False)
+    one = dreams.visual_importance_workspace_size(B, Hkv, vis) - 65536
+    assert dreams.prefill_visual_importance_workspace_size(B, Hkv, vis) >= 65536 + pieces * one
+    outs = []
+    for n in (None, pieces, pieces - 1):
+        ws = None if n is None else torch.zeros(65536 + n * one, dtype=torch.uint8, device=dev)
+        if n != 0:
+            outs.append(dreams.prefill_visual_importance(q, k, lens, lse, 0, vis, workspace=ws))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    for o in outs[2:]:
+        assert not torch.equal(outs[0], o)
+        assert torch.allclose(outs[0], o, rtol=3e-5, atol=0.0)
+
+
 def test_prefill_empty_prompt(dev):
     # a sequence with no prompt: every row -inf / 0, importance 0, and it does not count in AE
     p = W.make_prompt(2, 4, 4, 128, (0, 90), 0, 80, num_rows=96, seed=62)
