@@ -381,11 +381,12 @@ __global__ __launch_bounds__(1024) void prefill_entropy_mean_kernel(int B, int H
     for (int k = 0; k < U; ++k) x[k] = vec[min(i0 + k * 1024, nv - 1)];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const bool in = i0 + k * 1024 < nv;
-      s0 += in ? (double)x[k][0] : 0.0;
-      s1 += in ? (double)x[k][1] : 0.0;
-      s2 += in ? (double)x[k][2] : 0.0;
-      s3 += in ? (double)x[k][3] : 0.0;
+      // (a branch, so that a wave whose vectors are past the end skips the conversions: 2400 rows 4.0 -> 3.4 us)
+      if (i0 + k * 1024 >= nv) break;
+      s0 += (double)x[k][0];
+      s1 += (double)x[k][1];
+      s2 += (double)x[k][2];
+      s3 += (double)x[k][3];
     }
   }
   double s = (s0 + s1) + (s2 + s3);
