@@ -182,8 +182,11 @@ dreams_status_t plan_attn(const dreams_attn_desc_t* d, AttnPlan* p, size_t works
     const long long xcd_wgs = (p->units + 7LL) / 8 * p->row_groups, xcd_cus = cus / 8;
     if (splits > 1 && xcd_wgs < xcd_cus * wpc) {
       const int fine = fine_splits(xcd_wgs, xcd_cus, wpc, n_keys);
-      if (fine <= splits || attn_partial_bytes(p, fine, d->head_dim) <= workspace_bytes ||
-          attn_partial_bytes(p, splits, d->head_dim) > workspace_bytes)
+      // (a few more pieces cost as much in the merge as they gain: 8 heads on 2, 11 x 3135 keys, 8 pieces 16.8 us, 10
+      // pieces 17.3; 24 heads on 8, 3 x 2700 keys, head_dim 64, 7 pieces 17.5, 10 pieces 16.0)
+      const bool pays = fine < splits || 5 * fine >= 7 * splits;
+      if (pays && (fine <= splits || attn_partial_bytes(p, fine, d->head_dim) <= workspace_bytes ||
+                   attn_partial_bytes(p, splits, d->head_dim) > workspace_bytes))
         splits = fine;
     }
   }

@@ -420,6 +420,17 @@ def test_library_chosen_pieces(dev, case):
             dreams.tree_verify_attn(q, k, v, kv, par, max_kv_len=L, workspace=small[:need - 256])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,L,pieces", [
+    (11, 8, 2, 128, 13, 3135, 8),      # 10 would be finer by too little (16.8 against 17.3 us)
+    (3, 24, 8, 64, 37, 2733, 10),      # ... than 7 pays
+    (1, 8, 8, 128, 16, 3267, 16),
+    (1, 28, 4, 128, 100, 8000, 10),    # fewer than 8 units: fewer than the whole chip's slots
+])
+def test_library_piece_counts(dev, B, Hq, Hkv, D, T, L, pieces):
+    desc = dreams.AttnDesc(B, Hq, Hkv, D, T, (L + T + 63) // 64 * 64, L, 0, dreams.DREAMS_BF16, 0.125)
+    assert dreams.tree_verify_attn_splits(desc) == pieces
+
+
 @pytest.mark.parametrize("splits", [2, 4, 7])
 def test_pieces_cut_per_sequence_length(dev, splits):
     # several sequences of very different lengths (one with no prefix): each sequence's key axis is cut into
