@@ -213,7 +213,8 @@ dreams_status_t plan_attn(const dreams_attn_desc_t* d, AttnPlan* p, size_t works
 // ----------------------------------------------------------------------------------------- acceptance
 struct AcceptPlan {
   int chunks, chunk, groups, group_base, group_stride;
-  size_t val_off, idx_off, bytes;
+  size_t val_off, idx_off, bytes;   // bytes: what a call fills
+  size_t query_bytes;               // what the size query answers
 };
 
 // Pieces of a row: 8192 logits while the batch has fewer rows than about two workgroups per compute unit, so that
@@ -229,10 +230,10 @@ dreams_status_t plan_accept(int32_t B, int32_t T, int32_t V, AcceptPlan* p) {
   *p = AcceptPlan{};
   const long long rows = (long long)B * T;
   if (rows == 0) return DREAMS_OK;   // nothing to do, no workspace needed
-  long long chunks = (V + kAcceptLargePiece - 1) / kAcceptLargePiece;
+  long long chunks = ((long long)V + kAcceptLargePiece - 1) / kAcceptLargePiece;
   if (rows < kAcceptTargetWgs) {
     const long long want = (kAcceptTargetWgs + rows - 1) / rows;
-    const long long small = (V + kAcceptSmallPiece - 1) / kAcceptSmallPiece;
+    const long long small = ((long long)V + kAcceptSmallPiece - 1) / kAcceptSmallPiece;
     chunks = want < small ? want : small;
     if (chunks < 1) chunks = 1;
   }
@@ -263,17 +264,18 @@ dreams_status_t plan_accept(int32_t B, int32_t T, int32_t V, AcceptPlan* p) {
     p->group_base = 0;
     p->group_stride = 1;
   }
-  // (room for pieces of 32768 logits at least, so that a workspace sized for a large batch serves smaller ones,
-  // whose rows are cut into more pieces)
+  auto parts_bytes = [](long long parts) { return align_up((size_t)parts * 4, 256); };
+  p->val_off = kCounterBytes;
+  p->idx_off = p->val_off + parts_bytes(rows * chunks);
+  p->bytes = p->idx_off + parts_bytes(rows * chunks);
+  // (the query answers room for pieces of 32768 logits at least, so that a workspace sized for a large batch serves
+  // smaller ones, whose rows are cut into more pieces)
   long long room = ((long long)V + 32767) / 32768;
   if (room > kAcceptMaxChunks) room = kAcceptMaxChunks;
   long long unit = (V + room - 1) / room;
   unit = (unit + 3) / 4 * 4;
   room = (V + unit - 1) / unit;
-  const size_t parts = (size_t)rows * (chunks > room ? chunks : room);
-  p->val_off = kCounterBytes;
-  p->idx_off = p->val_off + align_up(parts * sizeof(float), 256);
-  p->bytes = p->idx_off + align_up(parts * sizeof(int32_t), 256);
+  p->query_bytes = kCounterBytes + 2 * parts_bytes(rows * (chunks > room ? chunks : room));
   return DREAMS_OK;
 }
 
@@ -480,7 +482,7 @@ dreams_status_t dreams_tree_accept_workspace_size(int32_t batch, int32_t num_nod
   AcceptPlan p;
   dreams_status_t st = plan_accept(batch, num_nodes, vocab, &p);
   if (st != DREAMS_OK) return st;
-  *bytes = p.bytes;
+  *bytes = p.query_bytes;
   return ok();
 }
 

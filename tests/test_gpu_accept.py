@@ -133,3 +133,28 @@ def test_unaligned_rows(dev, B, T, V):
         big[shift:shift + B * T * V] = to_dev(logits.reshape(-1), dev)
         run_and_compare(dev, logits, tokens, parent, "V=%d shift %d" % (V, shift),
                         logits_dev=big[shift:shift + B * T * V].view(B, T, V))
+
+
+@pytest.mark.parametrize("B,T,V,pieces", [(4, 100, 152064, 2), (5, 102, 70000, 2), (9, 60, 300000, 2), (1, 60, 32000, 4)])
+def test_workspace_of_the_pieces_used(dev, B, T, V, pieces):
+    """A call asks for its counters and two words for every piece of a row that it cuts, no more; the size query
+    answers at least that."""
+    rng = np.random.default_rng(B * T)
+    parent = np.stack([W.random_tree(rng, T, 6, 6) for _ in range(B)])
+    g = torch.Generator(device=dev)
+    g.manual_seed(B * T)
+    logits = torch.randn((B, T, V), generator=g, device=dev)
+    tokens = rng.integers(0, V, (B, T)).astype(np.int32)
+    need = 65536 + 2 * ((B * T * pieces * 4 + 255) // 256 * 256)
+    assert dreams.tree_accept_workspace_size(B, T, V) >= need
+    ws = torch.zeros(need, dtype=torch.uint8, device=dev)
+    tk, pr = to_dev(tokens, dev), to_dev(parent, dev)
+    got = dreams.tree_accept(logits, tk, pr, want_target_argmax=True, workspace=ws)
+    ref = dreams.tree_accept(logits, tk, pr, want_target_argmax=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got[3].long(), logits.argmax(dim=2))
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
+    assert not ws[:65536].any()
+    with pytest.raises(dreams.DreamsError):
+        dreams.tree_accept(logits, tk, pr, workspace=ws[:need - 256])
