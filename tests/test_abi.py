@@ -325,3 +325,18 @@ def test_bindings_reject_bad_tensors_before_any_launch(D):
         D.tree_accept_lm_head(bf, torch.zeros((10, 256), dtype=torch.bfloat16), i32, i32)
     with pytest.raises(TypeError):
         D.tree_accept_lm_head(bf.float(), torch.zeros((10, 256), dtype=torch.bfloat16), i32, i32)
+
+
+def test_current_stream_with_and_without_the_raw_entry_point(D, monkeypatch):
+    import torch
+
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(D, "_raw_stream", lambda device: 100 + device)
+    assert D._stream(None) == 103
+    monkeypatch.setattr(D, "_raw_stream", None)
+    assert D._stream(None) == 4711
+    assert D._stream(Stream) == 4711
