@@ -41,7 +41,7 @@ typedef enum {
   DREAMS_OK = 0,
   DREAMS_ERR_INVALID_ARG = -1,  /* a host-visible argument is out of range or a required pointer is NULL */
   DREAMS_ERR_UNSUPPORTED = -2,  /* valid in principle but not built (e.g. a head_dim other than 64/128)   */
-  DREAMS_ERR_WORKSPACE = -3,    /* workspace NULL or smaller than the matching *_workspace_size           */
+  DREAMS_ERR_WORKSPACE = -3,    /* workspace NULL or too small (*_workspace_size bytes are always enough)  */
   DREAMS_ERR_HIP = -4,          /* the HIP runtime reported an error (device query or kernel launch)     */
   DREAMS_ERR_DEVICE = -5        /* a kernel of an earlier call flagged a failure (dreams_workspace_status) */
 } dreams_status_t;
@@ -119,11 +119,16 @@ typedef struct {
 
 /* Bytes of workspace dreams_tree_verify_attn needs for `desc` on the current device (0 if none: then the
  * call accepts a NULL workspace).  Non-zero when the key axis is cut into pieces: the pieces' partial
- * results live there, after the counter region every workspace starts with. */
+ * results live there, after the counter region every workspace starts with.
+ * Where the library chooses the pieces (num_splits 0), a call that brings less than this, but room for as many
+ * pieces as leave each 384 keys or more, is not refused: it is cut into those, and its results differ from those
+ * with a whole workspace by the pieces' rounding.  Results that must not depend on the workspace's size take
+ * num_splits from dreams_tree_verify_attn_splits. */
 dreams_status_t dreams_tree_verify_attn_workspace_size(const dreams_attn_desc_t* desc, size_t* bytes);
 
 /* Number of pieces dreams_tree_verify_attn cuts the key axis of every (sequence, KV head) into for `desc` on
- * the current device (desc->num_splits, clamped, or the library's choice when it is 0). */
+ * the current device (desc->num_splits, clamped, or the library's choice when it is 0, for a workspace of
+ * dreams_tree_verify_attn_workspace_size bytes). */
 dreams_status_t dreams_tree_verify_attn_splits(const dreams_attn_desc_t* desc, int32_t* splits);
 
 /*
@@ -150,8 +155,8 @@ dreams_status_t dreams_tree_verify_attn_splits(const dreams_attn_desc_t* desc, i
  *                                         node i.  Takes precedence over parent.
  *   out        device [B, Hq, T, D]      same dtype as q
  *   lse        device [B, Hq, T] float, or NULL
- *   workspace  device, >= dreams_tree_verify_attn_workspace_size bytes (see "Workspaces" above), or NULL
- *              when that size is 0.
+ *   workspace  device, >= dreams_tree_verify_attn_workspace_size bytes (see "Workspaces" above, and that
+ *              function for a smaller one), or NULL when that size is 0.
  * Arithmetic: bf16 products accumulated in fp32 on the matrix cores, softmax statistics in fp32, one
  * rounding of the probabilities to bf16 before the value product; output rounded to the nearest bf16.  With
  * more than one piece of the key axis (dreams_tree_verify_attn_splits), each piece's output is rounded to
