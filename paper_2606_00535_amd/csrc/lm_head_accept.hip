@@ -152,26 +152,19 @@ __global__ __launch_bounds__(FIN_THREADS) void lm_head_finish_kernel(LmHeadArgs 
 }
 
 // The 64-row kernel.  A stage is 64 hidden entries (128 bytes of a row).  Per stage, each wave copies its 16
-// weight rows into its ring slot (two wave-wide LDS-DMA copies of 8 rows x 128 bytes) and loads 16 bytes of the
-// tile's hidden rows per thread into registers (thread t: row t / 8, chunk t % 8); a stage's hidden rows are
-// written to one of three shared LDS buffers one stage before they are used, and a barrier publishes them.
-// Every vector-memory operation of the loop is issued by inline assembly and waited for by exact count: a
-// stage is issued DW - 1 stages ahead, and at stage s the wave waits for stage s + 1, leaving DW - 2 stages of
-// copies in flight.  The 16-byte chunk c of a row r sits at position c ^ (r % 8) of its 128-byte LDS row, so
-// that the 16 rows one operand read touches fall on distinct banks.
-constexpr int LM_WAVES = kLmTileSmall / 16, LM_SK = 64, LM_DW = 8, LM_XBUF = 3;
-constexpr int LM_WSLOT = 16 * LM_SK * 2, LM_XSTAGE = kLmTile * LM_SK * 2;
-constexpr size_t LM_LDS = (size_t)LM_WAVES * LM_DW * LM_WSLOT + (size_t)LM_XBUF * LM_XSTAGE;
-
-__device__ __forceinline__ void load16_async(bf16x8& dst, const void* src) {
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(dst) : "v"(src) : "memory");
-}
-// wait until at most N of this wave's vector-memory operations are outstanding; x (the data of a load issued
-// before them) is tied to the wait, so that no use of it is scheduled ahead of it
-template <int N>
-__device__ __forceinline__ void wait_vm_tied(bf16x8& x) {
-  asm volatile("s_waitcnt vmcnt(%1)" : "+v"(x) : "n"(N) : "memory");
-}
+// weight rows into its own ring slot and an eighth of the tile's hidden rows into a slot that all eight read (three
+// wave-wide LDS-DMA copies of 8 rows x 128 bytes).  Every vector-memory operation of the loop is such a copy, issued by
+// inline assembly and waited for by exact count: at stage s a wave waits until its copies of that stage have landed,
+// leaving DW - 2 stages of them in flight, and a barrier makes the hidden rows whole and retires every wave's reads of
+// stage s - 1, whose slot takes stage s + DW - 1.  The 16-byte chunk c of a row r sits at position c ^ (r % 8) of its
+// 128-byte LDS row, so that the 16 rows one operand read touches fall on distinct banks.
+// (The hidden rows came through registers before, loaded by inline assembly and written to LDS a stage ahead, with 8
+// weight slots.  Only the allocation of each build's registers kept loads in flight from being copied: other forms of
+// that loop were compiled with such copies.  This form is level or faster: 60 rows x 32000 x 4096 56.1 -> 55.3 us, x
+// 128256 x 4096 209 -> 203, 10 x 17000 x 4096 42.0 -> 38.9.)
+constexpr int LM_WAVES = kLmTileSmall / 16, LM_SK = 64, LM_DW = 6;
+constexpr int LM_WSLOT = 16 * LM_SK * 2, LM_XSLOT = kLmTile * LM_SK * 2;
+constexpr size_t LM_LDS = (size_t)LM_DW * (LM_WAVES * LM_WSLOT + LM_XSLOT);
 
 template <bool QUARTERS>
 __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArgs a) {
@@ -179,7 +172,7 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   static_assert(LM_LDS + 2 * LM_WAVES * kLmTile * 4 <= 160 * 1024, "LDS budget");
   extern __shared__ __attribute__((aligned(1024))) char lm_lds[];
   char* wring = lm_lds;                                         // [wave][DW][16 rows x 128 B]
-  char* xs = lm_lds + (size_t)LM_WAVES * LM_DW * LM_WSLOT;      // [3][64 rows x 128 B]
+  char* xs = lm_lds + (size_t)LM_WAVES * LM_DW * LM_WSLOT;      // [DW][64 rows x 128 B]
   __shared__ float best_v[LM_WAVES][kLmTile];
   __shared__ int best_i[LM_WAVES][kLmTile];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -195,15 +188,13 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   const __bf16* wsrc0 = a.weight + (size_t)min(n0 + crow, a.V - 1) * H + 8 * cchunk;
   const __bf16* wsrc1 = a.weight + (size_t)min(n0 + 8 + crow, a.V - 1) * H + 8 * cchunk;
   const uint32_t wring_lds = __builtin_amdgcn_readfirstlane(lds_addr(wring + (size_t)wave * LM_DW * LM_WSLOT));
-  // hidden piece of this thread: row t / 8 (clamped past the rows), chunk t % 8, written at c ^ (r % 8)
-  const int xr = threadIdx.x >> 3, xc = threadIdx.x & 7;
-  const __bf16* xsrc = a.hidden + (size_t)min(m0 + xr, a.M - 1) * H + 8 * xc;
-  const int xw = xr * 128 + ((xc ^ (xr & 7)) << 4);
+  // the wave's hidden rows: 8 w + lane / 8 of the tile (clamped past the rows), chunks placed alike
+  const __bf16* xsrc = a.hidden + (size_t)min(m0 + 8 * wave + crow, a.M - 1) * H + 8 * cchunk;
+  const uint32_t xs_lds = __builtin_amdgcn_readfirstlane(lds_addr(xs) + wave * 1024);
 
   // QUARTERS: a workgroup starts at quarter nt % 4 of the hidden axis and wraps round; each quarter has its own sums,
   // added in one order wherever the workgroup started, so equal weight rows of different tiles still tie.
   const int quarter = nstages / 4, start = QUARTERS ? (nt & 3) * quarter : 0;
-  bf16x8 hv[LM_DW];
   auto issue = [&](int slot, int s) {
     int ks = min(s, nstages - 1) + start;   // (stages past the end repeat the last one, unused)
     if (QUARTERS && ks >= nstages) ks -= nstages;
@@ -211,7 +202,7 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
     const uint32_t dst = wring_lds + slot * LM_WSLOT;
     copy16_to_lds<true>(dst, wsrc0 + k);
     copy16_to_lds<true>(dst + 1024, wsrc1 + k);
-    load16_async(hv[slot], xsrc + k);
+    copy16_to_lds<false>(xs_lds + slot * LM_XSLOT, xsrc + k);
   };
   f32x4 acc[4], done[3][4];   // the current quarter's sums; those of the quarters before it, the latest first
 #pragma unroll
@@ -229,7 +220,7 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
       }
     }
     const char* wst = wring + ((size_t)wave * LM_DW + slot) * LM_WSLOT;
-    const char* xst = xs + (size_t)(s % LM_XBUF) * LM_XSTAGE;
+    const char* xst = xs + (size_t)slot * LM_XSLOT;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       const int c = 4 * ks + quad;
@@ -243,31 +234,18 @@ __global__ __launch_bounds__(64 * LM_WAVES) void lm_head_argmax_kernel(LmHeadArg
   };
 #pragma unroll
   for (int j = 0; j < LM_DW - 1; ++j) issue(j, j);
-  wait_vm_tied<3 * (LM_DW - 2)>(hv[0]);   // stage 0 has landed
-  *(bf16x8*)(xs + xw) = hv[0];
-  // Stage s: its slot's registers and ring slot take stage s + DW - 1 (the slot held stage s - 1, whose
-  // weights were read by this wave's products and whose hidden rows went to LDS before); stage s + 1 lands and
-  // its hidden rows go to their LDS buffer; the barrier publishes them and retires every wave's reads of the
-  // buffer stage s + 2 will take; then stage s is computed.
   for (int s0 = 0; s0 < nstages; s0 += LM_DW) {
 #pragma unroll
     for (int j = 0; j < LM_DW; ++j) {
       const int s = s0 + j;
       if (s >= nstages) break;
-      issue((j + LM_DW - 1) % LM_DW, s + LM_DW - 1);
-      wait_vm_tied<3 * (LM_DW - 2)>(hv[(j + 1) % LM_DW]);
-      *(bf16x8*)(xs + (size_t)((s + 1) % LM_XBUF) * LM_XSTAGE + xw) = hv[(j + 1) % LM_DW];
+      wait_vm<3 * (LM_DW - 2)>();
       barrier_lds();
+      issue((j + LM_DW - 1) % LM_DW, s + LM_DW - 1);
       compute(j, s);
     }
   }
-  // copies issued past the last stage land before the workgroup's LDS is released, loads before their registers are
-  // used for anything else
-  asm volatile("s_waitcnt vmcnt(0)"
-               : "+v"(hv[0]), "+v"(hv[1]), "+v"(hv[2]), "+v"(hv[3]), "+v"(hv[4]), "+v"(hv[5]), "+v"(hv[6]), "+v"(hv[7])
-               :
-               : "memory");
-  static_assert(LM_DW == 8, "every load register is tied to the wait");
+  wait_vm<0>();   // copies issued past the last stage land before the workgroup's LDS is released
   // (q0 + q1) + (q2 + q3) of the quarters in the row's own order; the first one taken was quarter nt % 4
 #pragma unroll
   for (int r = 0; r < (QUARTERS ? 4 : 0); ++r)

@@ -136,6 +136,21 @@ def test_ties_go_to_the_smallest_index(dev):
     np.testing.assert_array_equal(gam, ref_am)
 
 
+@pytest.mark.parametrize("stages", [4, 8, 12, 16, 20, 24, 36])
+def test_stages_of_the_ring(dev, stages):
+    """Hidden sizes on either side of whole turns of the six-slot ring, a last tile of few entries and odd rows."""
+    rng = np.random.default_rng(stages)
+    B, T, H, V = 1, 37, 64 * stages, 401
+    hid, wt = draw(rng, B, T, H, V)
+    _, logits, bound = expected_argmax(hid, wt)
+    parent = W.random_tree(rng, T, 4, 3)[None]
+    _, _, _, am = dreams.tree_accept_lm_head(to_bf16_dev(hid, dev), to_bf16_dev(wt, dev),
+                                             torch.zeros((B, T), dtype=torch.int32, device=dev),
+                                             torch.from_numpy(parent).to(dev), want_target_argmax=True)
+    torch.cuda.synchronize()
+    check_argmax(am.cpu().numpy().reshape(-1), logits, bound, "%d stages" % stages)
+
+
 @pytest.mark.parametrize("H,V", [(256, 900), (1280, 900), (2304, 900), (2048, 20000)])
 def test_equal_rows_of_different_tiles_tie(dev, H, V):
     """One weight row repeated in every tile (at H = 2048 the tiles start at different quarters of the hidden axis):
