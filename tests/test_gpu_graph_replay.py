@@ -13,6 +13,7 @@ import torch
 from gpu_util import device, layer_tensors, note, to_dev
 from paper_2606_00535_amd import dreams
 from paper_2606_00535_amd import workload as W
+from test_gpu_sampled import planned
 
 pytestmark = pytest.mark.gpu
 REPLAYS = 3
@@ -87,15 +88,15 @@ def test_tree_accept(dev, B, T, V):
                          list(eager), [ws], "tree_accept")
 
 
-@pytest.mark.parametrize("B,T,V,sub", [(1, 60, 32000, 1), (4, 128, 65536, 4)],
-                         ids=["row_pieces", "split_pieces"])
-def test_tree_accept_sampled(dev, B, T, V, sub):
-    # 1x60x32000 takes pieces of 4096 entries per row; 4x128x65536 is past the workgroup count where pieces of
-    # 8192 entries in four parts take over
+@pytest.mark.parametrize("B,T,V,form,depth", [
+    (1, 60, 32000, "rows", 8), (4, 128, 65536, "either", 8), (4, 128, 65536, "either", 100), (40, 5, 50000, "walk", 3),
+    (1, 6, 693128, "streamed", 3)], ids=["rows", "walked_or_by_rows", "by_rows_or_walked", "walk", "streamed"])
+def test_tree_accept_sampled(dev, B, T, V, form, depth):
+    assert planned(B, T, V)[0] == form and (form != "either" or (depth < planned(B, T, V)[1]) == (depth == 8))
     g = torch.Generator(device=dev)
     g.manual_seed(72)
     rng = np.random.default_rng(72)
-    par_h = random_tree(rng, B, T, 8, 4)
+    par_h = random_tree(rng, B, T, depth, 4)
     pr = to_dev(par_h, dev)
     tl = torch.randn((B, T, V), generator=g, device=dev) * 3
     dl = tl + torch.randn((B, T, V), generator=g, device=dev)
@@ -108,7 +109,7 @@ def test_tree_accept_sampled(dev, B, T, V, sub):
     note("sampled B=%d T=%d V=%d: accepted %s" % (B, T, V, eager[0].cpu().numpy()))
     replay_matches_eager(dev, lambda o: dreams.tree_accept_sampled(tl, dl, tk, pr, uni, tau, outputs=tuple(o),
                                                                    workspace=ws),
-                         list(eager), [ws], "tree_accept_sampled (%d parts a piece)" % sub)
+                         list(eager), [ws], "tree_accept_sampled (%s)" % form)
 
 
 def test_tree_accept_lm_head(dev):

@@ -2,6 +2,9 @@
 tokens on the workloads' seeded sampled inputs (draft = target + noise, children drawn from the draft), at
 several temperatures, on ragged and misaligned vocabularies, degenerate trees, and in the limits where the rule
 reduces to something simpler (identical models; low temperature = the greedy kernel)."""
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -19,6 +22,26 @@ def dev():
     d = device()
     dreams.lib()
     return d
+
+
+HOST = os.path.join(os.path.dirname(__file__), "..", "paper_2606_00535_amd", "csrc", "dreams_api.hip")
+
+
+def planned(B, T, V):
+    """How the library places a call's work ("rows", "walk", "streamed": a walk of several parts a piece, "either") and
+    the nodes of the longest path that it walks: the planner's rule with the planner's constants, so that a change of
+    them does not leave a test on another form than it names."""
+    text = open(HOST).read()
+    start = int(re.search(r"kSampledWalkFrom = (\d+);", text)[1])
+    base, per_wg, visit, wide = (float(x) for x in re.search(
+        r"most = \(([\d.]+) \+ ([\d.]+) \* \(double\)wgs\) / \(([\d.]+) \+ V / ([\d.]+)\);", text).groups())
+    pieces = (V + 4095) // 4096
+    if B * T * pieces <= start and pieces <= 64:
+        return "rows", 0
+    visits = min(128, int((base + per_wg * B * T * pieces) / (visit + V / wide)))
+    if T > visits and pieces <= 64:
+        return "either", visits
+    return ("streamed" if V > 64 * 10240 else "walk"), visits
 
 
 def gpu_sampled(dev, tl, dl, tok, par, uni, tau, tl_dev=None, dl_dev=None, workspace=None):
@@ -176,15 +199,15 @@ def test_rejected_arguments(dev):
 
 
 @pytest.mark.parametrize("V", [20000, 20001])
-def test_large_pieces(dev, V):
-    """Enough rows that the vocabulary is cut into 8192-entry pieces (streamed in 2048-entry sub-pieces), with a
-    ragged last piece whose trailing sub-pieces lie wholly past the vocabulary; V = 20001 takes the scalar
-    loads."""
+def test_large_batch(dev, V):
+    """A large batch of trees up to 8 deep, walked in pieces of 4096 entries beside workgroups that would take long
+    paths' rows (and leave); V = 20001 takes the scalar loads."""
     B, T = 30, 128
-    assert B * T * ((V + 4095) // 4096) > 4096
+    form, visits = planned(B, T, V)
+    assert form == "either" and visits >= 9
     rng = np.random.default_rng(V)
     tl, dl, tok, par, uni = random_case(rng, B, T, V, 8, 6, noise=0.7)
-    run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "large pieces V=%d" % V)
+    run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "large batch V=%d" % V)
 
 
 def test_out_of_range_tokens_are_rejected(dev):
@@ -215,13 +238,17 @@ def test_out_of_range_tokens_are_rejected(dev):
     (40, 5, 110000),     # 10240, more workgroups than compute units
     (130, 9, 3000),      # a row in one workgroup
     (16, 40, 8192),
+    (200, 9, 3000),
+    (300, 8, 8000),
     (1, 6, 700000),      # several parts per piece, streamed
     (2, 5, 700001),
+    (1, 6, 693128),      # ... the last piece's second part wholly past the vocabulary
+    (2, 5, 693127),
 ])
 def test_walk_form(dev, B, T, V):
     """Enough row pieces (or a vocabulary too long for the row form) that each sequence is walked by its own
     workgroups, in every size of part; the workspace's counters return to zero."""
-    assert B * T * ((V + 4095) // 4096) > 1024 or V > 64 * 4096
+    assert planned(B, T, V)[0] in ("walk", "streamed" if V > 600000 else "either")
     rng = np.random.default_rng(V + B)
     tl, dl, tok, par, uni = random_case(rng, B, T, V, min(T - 1, 6), 4, noise=0.7)
     ws = torch.zeros(dreams.tree_accept_sampled_workspace_size(B, T, V), dtype=torch.uint8, device=dev)
@@ -286,3 +313,60 @@ def test_a_long_path_costs_the_same_kept_or_not(dev):
         assert torch.all(out[0] == (0 if dl is far else T - 1))
     note("a chain of %d: first draft rejected %.1f us, all kept %.1f us" % (T, us[0], us[1]))
     assert us[1] <= 2.0 * us[0]
+
+
+# multi-piece shapes in which a star is walked, all of its children tested one after the other
+STARS = [(4, 128, 20000, "either"), (4, 128, 20001, "either"), (60, 24, 40000, "walk"), (1, 12, 693128, "streamed")]
+
+
+@pytest.mark.parametrize("B,T,V,form", STARS, ids=lambda x: str(x))
+def test_walked_star(dev, B, T, V, form):
+    """A node of many children: drafts that the target gives some mass, then drafts that it gives none, every one of
+    them rejected and the emitted token from the residual after all of them."""
+    assert planned(B, T, V)[0] == form
+    rng = np.random.default_rng(T + V)
+    par = np.tile(W.star_tree(T), (B, 1))
+    tl = rng.standard_normal((B, T, V), dtype=np.float32) * 3
+    dl = tl + 2 * rng.standard_normal((B, T, V), dtype=np.float32)
+    tok = rng.integers(0, V, (B, T)).astype(np.int32)
+    uni = rng.random((B, T)).astype(np.float32)
+    ws = torch.zeros(dreams.tree_accept_sampled_workspace_size(B, T, V), dtype=torch.uint8, device=dev)
+    ws[65536:] = 0xA5
+    run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "star", workspace=ws)
+    tl[:, :, :1000] -= 60.0
+    tok = rng.integers(0, 1000, (B, T)).astype(np.int32)
+    ra = run_and_compare(dev, tl, dl, tok, par, uni, 1.0, "star, all rejected", workspace=ws)
+    assert np.all(ra == 0) and not ws[:65536].any()
+
+
+@pytest.mark.parametrize("B,T,V,form,depth", [(44, 64, 20000, "walk", 63), (1, 6, 693128, "streamed", 5),
+                                              (4, 128, 20000, "either", 127), (80, 12, 16385, "walk", 11)])
+def test_kept_chain(dev, B, T, V, form, depth):
+    """Long walks: every draft of a chain is kept."""
+    assert planned(B, T, V)[0] == form
+    rng = np.random.default_rng(T + V + 1)
+    par = np.tile(W.chain_tree(T), (B, 1))
+    tl = rng.standard_normal((B, T, V), dtype=np.float32) * 3
+    tok = np.zeros((B, T), np.int32)
+    tok[:, 1:] = tl[:, :-1].argmax(axis=2)
+    uni = rng.random((B, T)).astype(np.float32)
+    ra = run_and_compare(dev, tl, tl, tok, par, uni, 1.0, "kept chain")
+    assert np.all(ra == depth)
+
+
+@pytest.mark.parametrize("B,T,V,form,depth", [(4, 40, 30001, "either", 5), (60, 10, 40001, "walk", 5),
+                                              (4, 60, 30001, "either", 40), (1, 6, 693129, "streamed", 3)])
+def test_tokens_that_no_piece_holds(dev, B, T, V, form, depth):
+    """As test_out_of_range_tokens_are_rejected, in the forms that exchange decisions between pieces."""
+    assert planned(B, T, V)[0] == form
+    rng = np.random.default_rng(V + depth)
+    tl, dl, tok, par, uni = random_case(rng, B, T, V, depth, 4)
+    bad = rng.random((B, T)) < 0.3
+    bad[:, 0] = False
+    tok_bad = np.where(bad, np.where(rng.random((B, T)) < 0.5, V, -1), tok).astype(np.int32)
+    tl[:, :, V - 1] = -1e4                         # token V - 1 now has exactly zero mass at every node
+    tok_ref = np.where(bad, V - 1, tok).astype(np.int32)
+    ga, gp, gn = gpu_sampled(dev, tl, dl, tok_bad, par, uni, 1.0)
+    ra, rp, rn = oracle.tree_accept_sampled(tl, dl, tok_ref, par, uni, 1.0)
+    assert np.array_equal(ga, ra) and np.array_equal(gp, rp) and np.array_equal(gn, rn)
+    assert np.all(gn != V - 1)

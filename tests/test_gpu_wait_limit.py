@@ -10,6 +10,7 @@ import oracle
 from gpu_util import ATTN_TOL_BF16, device, f32, layer_tensors, note, to_dev
 from paper_2606_00535_amd import dreams
 from paper_2606_00535_amd import workload as W
+from test_gpu_sampled import planned
 
 pytestmark = pytest.mark.gpu
 
@@ -22,9 +23,17 @@ def dev():
     dreams.set_wait_limit(0.2)
 
 
-def test_sampled_wait_gives_up_and_is_reported(dev):
-    wl = W.Workload(name="wait", batch=2, num_q_heads=2, num_kv_heads=2, head_dim=64, dtype="bf16", num_layers=1,
-                    kv_len=64, image_tokens=0, num_nodes=40, depth=6, max_branch=4, vocab=20000, agree=0.7, seed=51)
+@pytest.mark.parametrize("B,T,depth,V,form", [
+    (2, 40, 6, 20000, "rows"),
+    (40, 5, 3, 50000, "walk"),
+    (4, 60, 6, 20000, "either"),       # trees that are walked
+    (4, 60, 40, 20000, "either"),      # trees that are not
+    (1, 6, 3, 693128, "streamed"),
+])
+def test_sampled_wait_gives_up_and_is_reported(dev, B, T, depth, V, form):
+    assert planned(B, T, V)[0] == form
+    wl = W.Workload(name="wait", batch=B, num_q_heads=2, num_kv_heads=2, head_dim=64, dtype="bf16", num_layers=1,
+                    kv_len=64, image_tokens=0, num_nodes=T, depth=depth, max_branch=4, vocab=V, agree=0.7, seed=51)
     smp = W.make_sampled(wl)
     tl, dl = to_dev(smp.target_logits, dev), to_dev(smp.draft_logits, dev)
     tok, par, uni = to_dev(smp.tokens, dev), to_dev(smp.parent, dev), to_dev(smp.uniforms, dev)
