@@ -17,8 +17,8 @@
 //     32-key blocks that cross the diagonal or the prompt's end are masked, in a loop of their own (in one loop
 //     the two paths' states met in register copies).  Workgroups are ordered so that the row blocks with the
 //     most keys start first; a single round's second half takes them in the opposite order.
-//     What bounds it is the vector ALU (77 % of its issue slots: per score an fma, an exp2 at a quarter rate,
-//     an add and an fma, beside a quarter of a matrix instruction), as long as every compute unit holds two
+//     What bounds it is the vector ALU (active in 74 % of the cycles a compute unit is busy: per score an fma, an
+//     exp2 at a quarter rate, an add and an fma, beside a quarter of a matrix instruction), as long as every compute unit holds two
 //     workgroups to the end: with few workgroups, 256-row ones leave the longest alone with two waves a SIMD.  3136 rows x 32
 //     heads x 128: 85 us as 256-row workgroups, 72 us as 128-row ones, 63 us with the masked blocks apart, the
 //     maxima as three-input chains and the reference test on unscaled products (kernel times).
@@ -364,7 +364,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_stats_kernel(PrefillAr
 // Mean of the prompt rows' entropies: sum over [B, Hq, N] (rows past n_b hold 0) / (Hq * sum_b n_b), fp64, in a
 // fixed order (each thread a fixed stride of 16-byte vectors and the single entries at unaligned ends, then a tree
 // over the threads).  One workgroup, bound by memory latency: 8 vectors a thread in flight (a load at a time took
-// 26 us for 32 heads x 3136 rows; this form 8 us).
+// 26 us for 32 heads x 3136 rows; this form 6.4 us,
+// 6.9 right after the statistics).
 __global__ __launch_bounds__(1024) void prefill_entropy_mean_kernel(int B, int Hq, int N, const float* entropy,
                                                                     const int32_t* prompt_len, float* ae) {
   constexpr int U = 8;
@@ -378,10 +379,16 @@ __global__ __launch_bounds__(1024) void prefill_entropy_mean_kernel(int B, int H
   for (long long i0 = tid; i0 < nv; i0 += U * 1024) {
     f32x4 x[U];
 #pragma unroll
-    for (int k = 0; k < U; ++k) x[k] = vec[min(i0 + k * 1024, nv - 1)];
+    for (int k = 0; k < U; ++k) {
+      x[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (i0 + k * 1024 < nv) x[k] = vec[i0 + k * 1024];
+    }
+    // (all of them in flight together: without this the loads move behind the branches below, one latency each)
+    asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
+    static_assert(U == 8, "every vector is named");
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      // (a branch, so that a wave whose vectors are past the end skips the conversions: 2400 rows 4.0 -> 3.4 us)
+      // (a branch, so that a wave whose vectors are past the end skips the conversions: 8 heads x 300 rows 4.1 -> 3.6 us)
       if (i0 + k * 1024 >= nv) break;
       s0 += (double)x[k][0];
       s1 += (double)x[k][1];
