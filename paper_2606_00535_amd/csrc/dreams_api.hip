@@ -219,7 +219,8 @@ struct AcceptPlan {
 
 // Pieces of a row: 8192 logits while the batch has fewer rows than about two workgroups per compute unit, so that
 // the logits spread over the whole chip; otherwise whole rows (16 x 128 x 152064 in pieces of 16384: 211 us, 32768:
-// 204, 65536: 197, whole: 193), which need no second merge level either.
+// 204, 65536: 197, whole: 193), which need no second merge level either.  From 512 rows on that holds: 8 x 64 x 152064
+// 62 us in pieces of 32768, 53 whole; 9 x 60 x 32000 19.7, 14.6; 13 x 64 x 65536, the least even of those tried, 39.9, 40.2.
 constexpr int kAcceptSmallPiece = 8192, kAcceptLargePiece = 1 << 18, kAcceptTargetWgs = 512;
 constexpr int kAcceptGroups = 8;   // group counters per sequence (see tree_accept.hip)
 

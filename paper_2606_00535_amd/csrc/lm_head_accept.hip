@@ -450,9 +450,9 @@ hipError_t launch_lm_head_accept(const LmHeadArgs& a, hipStream_t stream) {
   else {
     // Workgroups keep in step.  Where their rows are multiples of 4 KB apart and they fill most of the chip, all of
     // them would read the same 1 KB of every row at a time, which the memory channels serve unevenly: they start at
-    // different quarters (60 rows x 32000 x 4096: 54.8 -> 44.3 us, 5.9 TB/s; 100000 x 2048: 125 -> 105 us).  Elsewhere
-    // that only costs (14 rows x 2496 x 1536 18.4 -> 19.7 us, 1 x 8000 x 4096 34.3 -> 36.3, 60 x 152064 x 3584
-    // 219 -> 228).
+    // different quarters (a call of 60 rows, 128256 x 4096: 233 -> 204 us; 100000 x 2048: 123 -> 102; 32000 x 2048: 40 ->
+    // 32).  Elsewhere that only costs (60 x 32000 x 1024 21.3 -> 23.9 us, x 128256 x 3072 152 -> 158, x 32000 x 5120 65.8
+    // -> 68.1; 10 x 8000 x 4096 32.1 -> 32.5).
     const hipError_t e = a.H % 2048 == 0 && 2LL * a.ntiles > a.cus ? launch_stream<true>(a, grid, stream)
                                                                    : launch_stream<false>(a, grid, stream);
     if (e != hipSuccess) return e;

@@ -239,7 +239,8 @@ hipError_t launch_f32(const AttnArgs& a, hipStream_t stream) {
 // Rows per workgroup: 1 while that leaves at most one workgroup per compute unit, then 2, then 4.  A workgroup of
 // 2 rows takes about 1.3 times, of 4 rows 2.2 times as long as one of 1 row, and a second round as long again
 // (us at 1, 2 and 4 rows:
-// 64 rows x 640 keys 6.4, 8.1, 13.8; 480 x 640 12.8, 9.2, 15.6; 1600 x 1300 65, 53, 49).
+// 64 rows x 640 keys 6.4, 8.1, 13.8; 480 x 640 12.8, 9.2, 15.6; 1600 x 1300 65, 53, 49).  At the 128 registers a lane
+// that 16 waves leave, 4 rows spill 11 (head_dim 64) or 13 (128) of them to scratch; those times include that.
 template <int D>
 hipError_t launch_f32_rows(const AttnArgs& a, hipStream_t stream) {
   const long long rows = (long long)a.units * a.G * a.T;

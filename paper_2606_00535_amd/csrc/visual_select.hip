@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void visual_importance_kernel(VisualArgs a) {
 // so that the blocks with the most rows (the first tokens) start first and share a compute unit with those
 // with the fewest.  The rows of a block are cut into `pieces` runs of stages, a workgroup each, where the blocks of
 // all KV heads are too few or too unequal to keep two workgroups on every compute unit: LLaVA-7B's prompt (384
-// blocks of 1 to 49 stages) 95 us a call in one piece, 74 us in two; 28 query heads on 4 KV heads x 2000 rows (32
+// blocks of 1 to 49 stages) 78 us a call in one piece, 62 us in two; 28 query heads on 4 KV heads x 2000 rows (32
 // blocks) 321 us in one, 32 us in 16.  (Blocks of fewer tokens instead, the rows shared by the waves: 91 and 84 us,
 // as every block reads all of the rows.)
 namespace pf {
