@@ -552,13 +552,12 @@ struct SampledPlan {
 // 4 x 60 of 32000 383, 71, 69 us; 8 x 60 of 32000 386, 117, 114; 60 of 152064 483, 95, 97; 2 x 128 of 32000 818, 78,
 // 77; 128 of 152064 1023, 190, 125; 4 x 128 of 152064 1085, 740, 430.  Trees up to 8 deep take what they took when
 // every call was walked (25 to 100 us, within 5 %).
-// Vocabularies beyond 64 pieces of 4096 entries are always walked (24 kept drafts of 300000 entries 253 us, 8 of 700000
-// 231 us; 107 and 121 us before there was a walk).
+// Wider vocabularies too, by rows in the walk's own pieces: 24 of 300000 254, 75, 107; 8 of 700000 237, 90, 121; 60 of
+// 500000 642, 255, 159.
 int sampled_max_visits(long long wgs, int V) {
   const double most = (20.0 + 0.028 * (double)wgs) / (6.2 + V / 85000.0);
   return most < kMaxNodes ? (int)most : kMaxNodes;
 }
-constexpr int kSampledEitherWgs = 2;   // row-form workgroups a compute unit holds where either form may be taken
 
 // cus: compute units of the device (the workspace's size does not depend on it)
 dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPlan* p) {
@@ -596,22 +595,6 @@ dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPl
     p->form = kSampledWalk;
     p->clusters = 1;
     p->max_visits = sampled_max_visits(wgs, V);
-    const long long n = pieces(part), masses = (long long)rows * n * 8;
-    if (T > p->max_visits && n <= kSampledMaxPieces) {
-      // two workgroups a compute unit, as the registers allow; the pieces' slots, then the rows' masses
-      long long clusters = kSampledEitherWgs * (long long)cus / (B * n);
-      const long long held = (room - masses - 256) / (B * n * kSampledManySlotBytes);
-      if (clusters > held) clusters = held;
-      if (clusters > T) clusters = T;
-      if (clusters > 1) {
-        p->form = kSampledEither;
-        p->clusters = (int)clusters;
-        p->mass_off = p->slot_off + align_up((size_t)(clusters * B * n * kSampledManySlotBytes), 256);
-        const long long small = pieces(kSampledParts[0]);
-        if (small <= kSampledMaxPieces && B * small <= cus) part = kSampledParts[0];
-        p->walk_chunks = (int)pieces(part);
-      }
-    }
   }
   auto fits = [&] {
     const long long n = pieces(part * sub);
@@ -629,7 +612,30 @@ dreams_status_t plan_sampled(int32_t B, int32_t T, int32_t V, int cus, SampledPl
       for (sub = 2; !fits();) ++sub;
     }
   }
-  const long long chunks = pieces(p->form == kSampledEither ? kSampledRowPart : part * sub);
+  long long chunks = pieces(part * sub);
+  if (p->form == kSampledWalk && T > p->max_visits) {
+    // rows in pieces of 4096 entries, two workgroups a compute unit as the registers allow, and a walk's of 2048 where the
+    // batch's take a unit each; for vocabularies that those do not hold, both in the walk's pieces, one a unit.  Their
+    // slots, then the rows' masses
+    const bool small = pieces(kSampledRowPart) <= kSampledMaxPieces;
+    const long long n = small ? pieces(kSampledRowPart) : chunks, masses = (long long)rows * n * 8;
+    long long clusters = (small ? 2LL : 1LL) * cus / (B * n);
+    const long long held = (room - masses - 256) / (B * n * kSampledManySlotBytes);
+    if (clusters > held) clusters = held;
+    if (clusters > T) clusters = T;
+    if (clusters > 1) {
+      p->form = kSampledEither;
+      p->clusters = (int)clusters;
+      p->mass_off = p->slot_off + align_up((size_t)(clusters * B * n * kSampledManySlotBytes), 256);
+      if (small) {
+        const long long two = pieces(kSampledParts[0]);
+        part = two <= kSampledMaxPieces && B * two <= cus ? kSampledParts[0] : kSampledRowPart;
+        sub = 1;
+      }
+      p->walk_chunks = (int)pieces(part * sub);
+      chunks = n;
+    }
+  }
   size_t stride = 16;
   while (stride > 4 && base + rows * stride > kMaxCounters) stride >>= 1;
   p->part = (int)part;

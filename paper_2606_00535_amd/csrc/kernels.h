@@ -199,7 +199,8 @@ hipError_t launch_tree_accept(const AcceptArgs& a, hipStream_t stream);
 // sequence's walk visits, one after the other: pieces of one part (2048 to 10240 entries, whose probabilities
 // stay in registers) or, for vocabularies that this does not hold, of several parts of 8192.  Either form: the
 // workgroups of a walk (pieces of 2048 or 4096 entries), then those of `clusters` clusters a sequence, which take its
-// rows in turn (pieces of 4096); by the length of the tree's paths, one or the other leaves at once.
+// rows in turn (pieces of 4096), both in the walk form's pieces for vocabularies that those do not hold; by the length
+// of the tree's paths, one or the other leaves at once.
 enum SampledForm { kSampledRows, kSampledWalk, kSampledEither };
 constexpr int kSampledRowPart = 4096;
 constexpr int kSampledParts[] = {2048, 4096, 8192, 10240};

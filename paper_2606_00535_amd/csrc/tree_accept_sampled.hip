@@ -36,10 +36,11 @@
 // Probabilities are fp64, so that the integer outcome is decided in the precision of the definition; exp is
 // Tang's table-driven method.
 //
-// Exchange.  The pieces of a row (row form), of several rows (either form) or of a sequence (walk form) are a cluster.  In step s = 1, 2, ... (a row's
-// statistics, and in the walk form every child tested) every piece stores its few words, each 48 bits of data beside the step's number, to its own slot, and one wave
-// polls all slots of the cluster, lane k the slot of piece k, until every word carries the step's number: one
-// store and one load of latency, with no counter in between.  Slots alternate between two places: a piece
+// Exchange.  The pieces of a row (row form), of several rows (either form) or of a sequence (walk form) are a
+// cluster.  In step s = 1, 2, ... (a row's statistics, and in the walk form every child tested) every piece stores its
+// few words, each 48 bits of data beside the step's number, to its own slot, and one wave polls all slots of the
+// cluster, lane k the slot of piece k, until every word carries the step's number: one store and one load of latency,
+// with no counter in between.  Slots alternate between two places: a piece
 // writes step s + 2 only after it has read every piece's step s + 1, which each wrote after reading step s.
 // A slot holds anything at entry; each piece clears its own and counts itself in on the cluster's counter, and
 // nobody reads a slot before that count is whole (the pieces that left are counted apart, so that it means what it
@@ -810,13 +811,13 @@ __device__ __forceinline__ bool path_longer_than(const int* par, int T, int most
 // First a workgroup per piece of every sequence's walk (EW entries a thread), which leave where the tree has longer
 // paths; then workgroups (c, b, j), piece j (ER entries a thread) of sequence b's cluster c, which takes rows c,
 // c + clusters, ..., and leave where it has not.  A sequence's walk has the slots of its clusters.
-template <bool VEC, int NT, int EW, int ER>
+template <bool VEC, bool HOLD, int NT, int EW, int ER>
 __global__ __launch_bounds__(NT, 4) void tree_accept_sampled_either_kernel(SampledArgs a) {
   __shared__ Shared sh;
   const int n = (int)blockIdx.x, walkers = a.B * a.walk_chunks;
   if (n < walkers) {
     const int b = n / a.walk_chunks, j = n - b * a.walk_chunks;
-    Piece<VEC, true, true, true, NT, EW> pc(a, sh, b, j, a.walk_chunks, a.seq_ctr + b,
+    Piece<VEC, true, true, HOLD, NT, EW> pc(a, sh, b, j, a.walk_chunks, a.seq_ctr + b,
                                             (size_t)b * a.clusters * a.chunks);
     pc.load(0);
     start_walk(a, sh, b);
@@ -827,7 +828,7 @@ __global__ __launch_bounds__(NT, 4) void tree_accept_sampled_either_kernel(Sampl
   }
   const int r = (n - walkers) / a.chunks, j = n - walkers - r * a.chunks;
   const int c = r / a.B, b = r - c * a.B;
-  Piece<VEC, false, true, true, NT, ER> pc(a, sh, b, j, a.chunks, row_counter(a, b, c),
+  Piece<VEC, false, true, HOLD, NT, ER> pc(a, sh, b, j, a.chunks, row_counter(a, b, c),
                                            ((size_t)b * a.clusters + c) * a.chunks);
   start_walk(a, sh, b);
   if (!path_longer_than(sh.par, a.T, a.max_visits)) return;
@@ -853,13 +854,20 @@ hipError_t launch_tree_accept_sampled(const SampledArgs& a, hipStream_t stream) 
   if (a.form == kSampledRows)
     return a.vec4 ? go(tree_accept_sampled_rows_kernel<true, 512, 8>, 512)
                   : go(tree_accept_sampled_rows_kernel<false, 512, 8>, 512);
+#define DREAMS_EITHER(HOLD, NT, EW, ER)                                               \
+  return a.vec4 ? go(tree_accept_sampled_either_kernel<true, HOLD, NT, EW, ER>, NT)   \
+                : go(tree_accept_sampled_either_kernel<false, HOLD, NT, EW, ER>, NT)
   if (a.form == kSampledEither) {
-    if (a.part == 4 * 512)
-      return a.vec4 ? go(tree_accept_sampled_either_kernel<true, 512, 4, 8>, 512)
-                    : go(tree_accept_sampled_either_kernel<false, 512, 4, 8>, 512);
-    return a.vec4 ? go(tree_accept_sampled_either_kernel<true, 512, 8, 8>, 512)
-                  : go(tree_accept_sampled_either_kernel<false, 512, 8, 8>, 512);
+    if (a.sub_pieces > 1) DREAMS_EITHER(false, 1024, 8, 8);
+    switch (a.part) {
+      case 2048: DREAMS_EITHER(true, 512, 4, 8);
+      case 4096: DREAMS_EITHER(true, 512, 8, 8);
+      case 8192: DREAMS_EITHER(true, 1024, 8, 8);
+      case 10240: DREAMS_EITHER(true, 1024, 10, 10);
+    }
+    return hipErrorInvalidValue;
   }
+#undef DREAMS_EITHER
 #define DREAMS_WALK(HOLD, NT, E)                                                        \
   return a.vec4 ? go(tree_accept_sampled_walk_kernel<true, HOLD, NT, E>, NT)            \
                 : go(tree_accept_sampled_walk_kernel<false, HOLD, NT, E>, NT)

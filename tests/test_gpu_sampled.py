@@ -28,9 +28,9 @@ HOST = os.path.join(os.path.dirname(__file__), "..", "paper_2606_00535_amd", "cs
 
 
 def planned(B, T, V):
-    """How the library places a call's work ("rows", "walk", "streamed": a walk of several parts a piece, "either") and
-    the nodes of the longest path that it walks: the planner's rule with the planner's constants, so that a change of
-    them does not leave a test on another form than it names."""
+    """How the library places a call's work ("rows", "walk" or "either"; with "streamed" where a piece is of several
+    parts) and the nodes of the longest path that it walks: the planner's rule with the planner's constants, so that a
+    change of them does not leave a test on another form than it names."""
     text = open(HOST).read()
     start = int(re.search(r"kSampledWalkFrom = (\d+);", text)[1])
     base, per_wg, visit, wide = (float(x) for x in re.search(
@@ -39,9 +39,7 @@ def planned(B, T, V):
     if B * T * pieces <= start and pieces <= 64:
         return "rows", 0
     visits = min(128, int((base + per_wg * B * T * pieces) / (visit + V / wide)))
-    if T > visits and pieces <= 64:
-        return "either", visits
-    return ("streamed" if V > 64 * 10240 else "walk"), visits
+    return ("either" if T > visits else "walk") + (" streamed" if V > 64 * 10240 else ""), visits
 
 
 def gpu_sampled(dev, tl, dl, tok, par, uni, tau, tl_dev=None, dl_dev=None, workspace=None):
@@ -244,11 +242,13 @@ def test_out_of_range_tokens_are_rejected(dev):
     (2, 5, 700001),
     (1, 6, 693128),      # ... the last piece's second part wholly past the vocabulary
     (2, 5, 693127),
+    (4, 4, 693128),
 ])
 def test_walk_form(dev, B, T, V):
     """Enough row pieces (or a vocabulary too long for the row form) that each sequence is walked by its own
     workgroups, in every size of part; the workspace's counters return to zero."""
-    assert planned(B, T, V)[0] in ("walk", "streamed" if V > 600000 else "either")
+    form, visits = planned(B, T, V)
+    assert visits > min(T - 1, 6) or V > 64 * 10240
     rng = np.random.default_rng(V + B)
     tl, dl, tok, par, uni = random_case(rng, B, T, V, min(T - 1, 6), 4, noise=0.7)
     ws = torch.zeros(dreams.tree_accept_sampled_workspace_size(B, T, V), dtype=torch.uint8, device=dev)
@@ -316,7 +316,8 @@ def test_a_long_path_costs_the_same_kept_or_not(dev):
 
 
 # multi-piece shapes in which a star is walked, all of its children tested one after the other
-STARS = [(4, 128, 20000, "either"), (4, 128, 20001, "either"), (60, 24, 40000, "walk"), (1, 12, 693128, "streamed")]
+STARS = [(4, 128, 20000, "either"), (4, 128, 20001, "either"), (60, 24, 40000, "walk"), (1, 12, 693128, "either streamed"),
+         (9, 6, 300000, "walk"), (4, 4, 700001, "walk streamed")]
 
 
 @pytest.mark.parametrize("B,T,V,form", STARS, ids=lambda x: str(x))
@@ -339,7 +340,9 @@ def test_walked_star(dev, B, T, V, form):
     assert np.all(ra == 0) and not ws[:65536].any()
 
 
-@pytest.mark.parametrize("B,T,V,form,depth", [(44, 64, 20000, "walk", 63), (1, 6, 693128, "streamed", 5),
+@pytest.mark.parametrize("B,T,V,form,depth", [(44, 64, 20000, "walk", 63), (1, 6, 693128, "either streamed", 5),
+                                              (1, 24, 300001, "either", 23), (1, 8, 600000, "either", 7),
+                                              (4, 4, 693128, "walk streamed", 3), (9, 6, 300000, "walk", 5),
                                               (4, 128, 20000, "either", 127), (80, 12, 16385, "walk", 11)])
 def test_kept_chain(dev, B, T, V, form, depth):
     """Long walks: every draft of a chain is kept."""
@@ -355,7 +358,8 @@ def test_kept_chain(dev, B, T, V, form, depth):
 
 
 @pytest.mark.parametrize("B,T,V,form,depth", [(4, 40, 30001, "either", 5), (60, 10, 40001, "walk", 5),
-                                              (4, 60, 30001, "either", 40), (1, 6, 693129, "streamed", 3)])
+                                              (4, 60, 30001, "either", 40), (1, 6, 693129, "either streamed", 3),
+                                              (1, 8, 300001, "either", 3), (4, 4, 693127, "walk streamed", 2)])
 def test_tokens_that_no_piece_holds(dev, B, T, V, form, depth):
     """As test_out_of_range_tokens_are_rejected, in the forms that exchange decisions between pieces."""
     assert planned(B, T, V)[0] == form

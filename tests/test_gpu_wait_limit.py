@@ -28,7 +28,9 @@ def dev():
     (40, 5, 3, 50000, "walk"),
     (4, 60, 6, 20000, "either"),       # trees that are walked
     (4, 60, 40, 20000, "either"),      # trees that are not
-    (1, 6, 3, 693128, "streamed"),
+    (4, 4, 2, 693128, "walk streamed"),
+    (1, 6, 5, 693128, "either streamed"),
+    (1, 24, 20, 300000, "either"),
 ])
 def test_sampled_wait_gives_up_and_is_reported(dev, B, T, depth, V, form):
     assert planned(B, T, V)[0] == form
