@@ -551,7 +551,9 @@ struct SampledPlan {
 // longer in wide rows.  Chains of which every draft is kept, walked, by rows, and by rows before there was a walk:
 // 4 x 60 of 32000 383, 71, 69 us; 8 x 60 of 32000 386, 117, 114; 60 of 152064 483, 95, 97; 2 x 128 of 32000 818, 78,
 // 77; 128 of 152064 1023, 190, 125; 4 x 128 of 152064 1085, 740, 430.  Trees up to 8 deep take what they took when
-// every call was walked (25 to 100 us, within 5 %).
+// every call was walked (25 to 100 us, within 5 %; 16 x 128 of 1000 27.4 us then, 29.2 now).  Where rows still
+// lose, a unit holds two of their workgroups, as the registers of a kernel of both kinds allow; the row form's holds
+// three.  Loading the next row ahead of a row's exchanges gains 4 % at 4 x 128 of 152064; not kept.
 // Wider vocabularies too, by rows in the walk's own pieces: 24 of 300000 254, 75, 107; 8 of 700000 237, 90, 121; 60 of
 // 500000 642, 255, 159.
 int sampled_max_visits(long long wgs, int V) {
